@@ -288,9 +288,13 @@ eogp_status eogp_sign_pack_tiled(const float* X, int64_t ldx, int64_t N, int64_t
  *   topk         1..256.
  *   ws           eogp_score_topk_workspace_size(N, Q, U, k_per_module, topk) bytes.
  *                With several modules it includes the exact per-(module,
- *                query, row) integer dots of one 16-query pass, U*16*N*4
- *                bytes (8 when some k_u > 2^16), which a second kernel
- *                turns into fp64 terms summed in module order.
+ *                query, row) integer dots of one pass, U*16*N*4 bytes (8 when
+ *                some k_u > 2^16), which a second kernel turns into fp64 terms
+ *                summed in module order. More than 16 queries run 32 to a
+ *                pass where topk <= 128 and no k_u > 2^16; the size reported
+ *                then holds the 32-query pass (twice the dots and candidate
+ *                lists). A smaller workspace that holds the 16-query pass is
+ *                accepted and runs 16 to a pass, with the same results.
  * Requirements: code_row_stride a multiple of 8 and codes 8-byte aligned;
  * Y finite. k_per_module is read on the host during the call (the module
  * table travels in kernel arguments); the call only enqueues work.
@@ -321,9 +325,10 @@ eogp_status eogp_score_topk_tiled(const uint8_t* codes, const uint16_t* scales, 
  * eogp_score_topk, with the workspace taken from a 128 MiB array that the
  * library holds in each GPU's memory until the process ends. The call
  * allocates nothing (no hipMalloc, hipFree or allocating library routine) and
- * only enqueues work on `stream`. Limit: the call's workspace size, as
- * eogp_score_topk_workspace_size reports it, must be at most 128 MiB
- * (134217728 bytes), else EOGP_ERR_INVALID with nothing enqueued. One
+ * only enqueues work on `stream`. Limit: the call's workspace with 16 queries
+ * to a pass must be at most 128 MiB (134217728 bytes; up to 16 queries, the
+ * size eogp_score_topk_workspace_size reports), else EOGP_ERR_INVALID with
+ * nothing enqueued. One
  * module of 16,384 bits fits any number of stored rows with up to 3,936
  * queries per call; several modules need 64 bytes per stored row and
  * module for each 16 queries (48 modules of 8,192 bits: about 38,000 rows for

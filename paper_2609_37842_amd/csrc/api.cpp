@@ -45,6 +45,7 @@ eogp_status srht_project(const float* Z, int64_t ldz, int64_t N, int64_t m, cons
                          size_t ws_bytes, hipStream_t s);
 const char* last_error_cstr();
 size_t score_ws(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk);
+size_t score_ws_min(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk);
 eogp_status score_topk(const uint8_t* codes, int64_t cstride, const uint16_t* scales, int64_t N,
                        int32_t U, const int64_t* kmod, const float* Y, int64_t ldy, int64_t Q,
                        int32_t topk, int64_t* out_idx, float* out_score, float* full, void* ws,
@@ -471,7 +472,7 @@ eogp_status eogp_score_topk(const uint8_t* codes, int64_t code_row_stride, const
   const eogp_status st = check_score_args(codes, code_row_stride, scales, N, U, k_per_module, Y,
                                           ldy, Q, topk, out_idx, out_score);
   if (st != EOGP_OK) return st;
-  if (ws_bytes < score_ws(N, Q, U, k_per_module, topk) || !ws)
+  if (ws_bytes < score_ws_min(N, Q, U, k_per_module, topk) || !ws)
     return fail(EOGP_ERR_WORKSPACE, "score_topk: workspace too small");
   return score_topk(codes, code_row_stride, scales, N, U, k_per_module, Y, ldy, Q, topk, out_idx,
                     out_score, full_scores, ws, ws_bytes, S(stream));
@@ -495,7 +496,7 @@ eogp_status eogp_score_topk_tiled(const uint8_t* codes, const uint16_t* scales, 
                                           topk, out_idx, out_score);
   if (st != EOGP_OK) return st;
   if ((uintptr_t)codes % 16 != 0) return fail(EOGP_ERR_INVALID, "score_topk_tiled: codes must be 16-byte aligned");
-  if (ws_bytes < score_ws(N, Q, U, k_per_module, topk) || !ws)
+  if (ws_bytes < score_ws_min(N, Q, U, k_per_module, topk) || !ws)
     return fail(EOGP_ERR_WORKSPACE, "score_topk_tiled: workspace too small");
   return score_topk_tiled(codes, scales, N, U, k_per_module, Y, ldy, Q, topk, out_idx, out_score,
                           full_scores, ws, ws_bytes, S(stream));
@@ -509,7 +510,7 @@ eogp_status eogp_score_topk_noalloc(const uint8_t* codes, int64_t code_row_strid
   eogp_status st = check_score_args(codes, code_row_stride, scales, N, U, k_per_module, Y, ldy, Q,
                                     topk, out_idx, out_score);
   if (st != EOGP_OK) return st;
-  const size_t need = score_ws(N, Q, U, k_per_module, topk);
+  const size_t need = score_ws_min(N, Q, U, k_per_module, topk);
   if (need > score_scratch_bytes())
     return fail(EOGP_ERR_INVALID, "score_topk_noalloc: this call needs " + std::to_string(need) +
                                       " bytes of scratch, more than the " +

@@ -9,34 +9,42 @@
 // s * (2 n1 - sum) * 2^-f is exact in fp64 and the terms are added in module
 // order, so the score is reproducible bit for bit.
 //
-// Data flow. A pass streams every stored code once for a group of 16
-// queries. v_mfma_i32_32x32x32_i8 takes the 32 plane rows (16 queries x
-// {h, l}) as its A operand and 32 stored rows as B, so one instruction
-// serves both planes and each lane ends with 8 queries of one stored row
-// (the h and l sums of a query land in the same lane). A 512-thread
-// workgroup (8 waves, 2 per SIMD) owns 512 consecutive rows at a time, each
-// wave two tiles of 32 rows. The modules are walked in steps of 512 bits;
-// per step each lane holds 32 bytes of its row (two 16-byte loads, requested
-// D steps ahead in a register ring), the workgroup stages the step's plane
-// fragments (16 KB) in LDS once, double-buffered, and every fragment read
-// from LDS feeds both tiles.
+// Data flow. A pass streams every stored code once for a group of NQT * 16
+// queries (NQT = 2: 32, the rule is in choose_cfg). v_mfma_i32_32x32x32_i8
+// takes the 32 plane rows of 16 queries ({h, l}) as its A operand and 32
+// stored rows as B, so one instruction serves both planes and each lane ends
+// with 8 queries of one stored row (the h and l sums of a query land in the
+// same lane). A 512-thread workgroup (8 waves, 2 per SIMD) owns 256 RT
+// consecutive rows at a time, each wave RT tiles of 32 rows. The modules are
+// walked in steps of 512 bits, each in two halves of 256: per half each lane
+// holds 16 bytes of each of its RT rows (requested two halves ahead), the
+// workgroup stages the half's plane fragments (8 KB per 16 queries) in LDS,
+// and every fragment read from LDS feeds RT MFMAs, every expanded code operand
+// NQT of them. The requests run on into the next block of rows, so a block's
+// last halves and its candidate pass cover the next one's first loads.
 //
-// Bit expansion. The 16 bytes c of a lane feed 8 MFMAs, one per bit
-// position t of a byte. The operand of MFMA t is (c >> s) & (0x01010101 <<
+// Bit expansion. The 16 bytes c of a lane feed 8 MFMAs per query tile, one per
+// bit position t of a byte. The operand of MFMA t is (c >> s) & (0x01010101 <<
 // w) with t = s + w, w = t mod NCLS: its bytes are 0 or 2^w, so the MFMA adds
 // 2^w times the wanted sum into accumulator class w, and n1 = sum_w acc_w /
-// 2^w (exact shifts: every term of acc_w is a multiple of 2^w). One shift
-// serves NCLS masks, and one 64-bit shift serves two words, so with NCLS = 2
-// expanding 16 bytes for their 8 MFMAs takes 32 ANDs and 6 shifts (a shift
-// and an AND per word and MFMA would take 64). The query planes are prepared
-// in exactly that order: byte j of lane (M, g) of MFMA (u, t) in step s of a
-// module holds coordinate 8 (64 s + 32 g + 16 u + j) + t.
+// 2^w (exact shifts: every term of acc_w is a multiple of 2^w). One 64-bit
+// shift serves two words, and with NCLS = 2 one shift serves two masks: 32 ANDs
+// and 6 shifts for 16 bytes; NCLS = 1 (NQT = 2, whose accumulators take the
+// registers of the second class) takes 32 ANDs and 14 shifts for twice as
+// many MFMAs. The query planes are prepared in exactly that order: byte j of
+// lane (M, g) of MFMA (u, t) in step s of a module holds coordinate 8 (64 s +
+// o + j) + t, where o = 32 g + 16 u for the tiled store (its 16-byte pieces)
+// and 32 u + 16 g for row-major rows (each half then reads 32 bytes of a row
+// together).
 //
 // After the last module the workgroup's scores are filtered against a
-// per-query threshold into an LDS candidate list (score desc, index asc). A
-// list that fills up is pruned to the top-k (bitonic sort) and the entries
-// that did not fit are inserted again, so no qualifying row is lost. Finally
-// each workgroup writes its top-k per query and a merge kernel reduces them.
+// per-query threshold into an LDS candidate list (score desc, index asc). The
+// threshold starts at the top-k-th largest of the first block's per-lane
+// maxima (that many rows reach it, so no row below it can be kept). A list
+// that fills up is pruned to its top-k by one wave (a bitwise search of the
+// k-th key over ballots, eight lists at a time) and the entries that did not
+// fit are offered again, so no qualifying row is lost. Finally each workgroup
+// writes its top-k per query and a merge kernel reduces them.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -51,21 +59,12 @@ namespace {
 constexpr int QB = 16;                 // queries per pass
 constexpr int NW = 8;                  // waves per workgroup
 constexpr int NTHR = NW * 64;
-constexpr int MCAP = 1024;             // candidate slots of the merge's list
-constexpr int MRU = 2;                 // candidates per thread per merge round
 constexpr int MSPLIT = 16;             // first-level merge workgroups per query
 constexpr int MAX_TOPK = 256;
 
-// A step covers SB bytes (8 SB bits) of a module in every row: lane (row,
-// g) holds SB / 2 of them as NU = SB / 32 16-byte words, which feed FR = 8 NU
-// MFMAs per tile, whose plane fragments take PU = 64 FR 16-byte slots (FR KB).
-template <int SB>
-struct StepShape {
-  static constexpr int NU = SB / 32;
-  static constexpr int FR = 8 * NU;
-  static constexpr int PU = 64 * FR;
-  static constexpr int PV = PU / NTHR;   // plane words staged per thread
-};
+constexpr int SB = 64;                 // bytes of a row per step
+constexpr int FRAGS = 16;              // plane fragments (1 KB) per step and 16 queries
+constexpr int HALF_U4 = 8 * 64;        // 16-byte slots of a half step's fragments per 16 queries
 
 typedef __attribute__((__vector_size__(16 * sizeof(int)))) int i32x16;
 template <typename T>
@@ -78,14 +77,12 @@ struct ModInfo {
   int32_t sbase;   // first step of the module
 };
 
-// Logical right shift of a register pair by s in one VALU instruction. The
-// compiler turns a 64-bit shift whose result is masked to bits that never
-// cross the halves back into two 32-bit shifts; here the bits that do cross
-// are masked away by the caller, so one instruction serves two words.
-__device__ __forceinline__ uint64_t shr_pair(uint64_t x, int s) {
-  uint64_t r;
-  asm("v_lshrrev_b64 %0, %1, %2" : "=v"(r) : "s"(s), "v"(x));
-  return r;
+// A shift amount the compiler does not know: a 64-bit shift by it stays one
+// instruction. (Of a shift by a known amount whose crossing bits are masked away
+// the compiler makes two 32-bit ones.)
+__device__ __forceinline__ int opaque_shift(int s) {
+  asm("" : "+s"(s));
+  return s;
 }
 
 __device__ __forceinline__ uint64_t order_key(double x) {
@@ -104,18 +101,22 @@ __device__ __forceinline__ bool before(uint64_t ka, uint32_t ia, uint64_t kb, ui
 // grid (16 * groups, U): per (query, module) the exponent f and the sum of
 // y_int, stored [group][U][16]; queries past Q get f = 0 and sum 0. The sum is
 // carried in 64 bits: |y_int| <= 2^14 and k_u <= 2^22 bound it by 2^36.
-__global__ __launch_bounds__(256) void k_query_stats(const float* __restrict__ Y, int64_t ldy,
-                                                     int64_t Q, int U,
-                                                     const ModInfo* __restrict__ mods,
-                                                     int32_t* __restrict__ fq,
-                                                     int64_t* __restrict__ ysum) {
-  __shared__ float smax[4];
-  __shared__ int64_t ssum[4];
+// One 512-thread workgroup, eight loads in flight per thread: with 256 threads
+// and one load at a time the chain of loads was the whole time (16 queries of
+// 16,384 coordinates 40 us; now 11 us).
+constexpr int STAT_THR = 512, STAT_UNR = 8;
+__global__ __launch_bounds__(STAT_THR) void k_query_stats(const float* __restrict__ Y, int64_t ldy,
+                                                          int64_t Q, int U,
+                                                          const ModInfo* __restrict__ mods,
+                                                          int32_t* __restrict__ fq,
+                                                          int64_t* __restrict__ ysum) {
+  __shared__ float smax[STAT_THR / 64];
+  __shared__ int64_t ssum[STAT_THR / 64];
   const int64_t q = blockIdx.x;
-  const int u = blockIdx.y;
+  const int u = blockIdx.y, tid = threadIdx.x;
   const int64_t o = ((q / QB) * U + u) * QB + (q % QB);
   if (q >= Q) {
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
       fq[o] = 0;
       ysum[o] = 0;
     }
@@ -124,11 +125,19 @@ __global__ __launch_bounds__(256) void k_query_stats(const float* __restrict__ Y
   const ModInfo md = mods[u];
   const float* y = Y + q * ldy + md.coff;
   float mx = 0.f;
-  for (int c = threadIdx.x; c < md.k; c += 256) mx = fmaxf(mx, fabsf(y[c]));
+  for (int c = tid; c < md.k; c += STAT_THR * STAT_UNR) {
+    float v[STAT_UNR];
+#pragma unroll
+    for (int e = 0; e < STAT_UNR; ++e) v[e] = y[min(c + e * STAT_THR, md.k - 1)];
+#pragma unroll
+    for (int e = 0; e < STAT_UNR; ++e) mx = fmaxf(mx, fabsf(v[e]));
+  }
   for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-  if ((threadIdx.x & 63) == 0) smax[threadIdx.x >> 6] = mx;
+  if ((tid & 63) == 0) smax[tid >> 6] = mx;
   __syncthreads();
-  mx = fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3]));
+  mx = smax[0];
+#pragma unroll
+  for (int w = 1; w < STAT_THR / 64; ++w) mx = fmaxf(mx, smax[w]);
   int f = 0;
   if (mx > 0.f) {
     int e;
@@ -137,13 +146,22 @@ __global__ __launch_bounds__(256) void k_query_stats(const float* __restrict__ Y
   }
   int64_t s = 0;
   if (mx > 0.f)
-    for (int c = threadIdx.x; c < md.k; c += 256) s += (int64_t)rintf(ldexpf(y[c], f));
+    for (int c = tid; c < md.k; c += STAT_THR * STAT_UNR) {
+      float v[STAT_UNR];
+#pragma unroll
+      for (int e = 0; e < STAT_UNR; ++e) v[e] = y[min(c + e * STAT_THR, md.k - 1)];
+#pragma unroll
+      for (int e = 0; e < STAT_UNR; ++e)
+        if (c + e * STAT_THR < md.k) s += (int64_t)rintf(ldexpf(v[e], f));
+    }
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-  if ((threadIdx.x & 63) == 0) ssum[threadIdx.x >> 6] = s;
+  if ((tid & 63) == 0) ssum[tid >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     fq[o] = f;
-    ysum[o] = ssum[0] + ssum[1] + ssum[2] + ssum[3];
+    int64_t t = 0;
+    for (int w = 0; w < STAT_THR / 64; ++w) t += ssum[w];
+    ysum[o] = t;
   }
 }
 
@@ -162,25 +180,23 @@ __global__ void k_mod_table(ModChunk c, ModInfo* __restrict__ mods) {
 
 // Planes laid out [group][step][MFMA f][lane][j] with f = 8 u + t: lane
 // (M, g) = (lane % 32, lane / 32) is plane M / 16 (0: h, 1: l) of query M % 16,
-// byte j holds coordinate 8 (sb s + sb / 2 g + 16 u + j) + t of the step's
-// module (0 past the module), sb = bytes per row and step. One thread per
-// (group, step, u, g, query, t) forms the 16 bytes of both planes of its query:
-// eight neighbouring threads (t = 0..7) read eight neighbouring coordinates.
+// byte j holds coordinate 8 (64 s + o + j) + t of the step's module (0 past the
+// module), o = 32 g + 16 u (tiled) or 32 u + 16 g. One thread per (group, step,
+// u, g, query, t) forms the 16 bytes of both planes of its query: eight
+// neighbouring threads (t = 0..7) read eight neighbouring coordinates.
 __global__ __launch_bounds__(256) void k_query_planes(const float* __restrict__ Y, int64_t ldy,
                                                       int64_t Q, int U,
                                                       const ModInfo* __restrict__ mods,
                                                       const int32_t* __restrict__ fq,
-                                                      int64_t n_steps, int64_t n_groups, int sb,
+                                                      int64_t n_steps, int64_t n_groups, int tiled,
                                                       int8_t* __restrict__ planes) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int nu = sb / 32;                                 // 16-byte words per lane and step
-  const int64_t per_step = 256 * (int64_t)nu;             // threads per step
-  if (idx >= n_groups * n_steps * per_step) return;
+  if (idx >= n_groups * n_steps * 512) return;
   const int t = (int)(idx & 7);
   const int qn = (int)((idx >> 3) & 15);
   const int g = (int)((idx >> 7) & 1);
-  const int uc = (int)((idx >> 8) % nu);
-  const int64_t gs = idx / per_step;
+  const int uc = (int)((idx >> 8) & 1);
+  const int64_t gs = idx >> 9;
   const int64_t step = gs % n_steps;
   const int64_t grp = gs / n_steps;
   int lo = 0, hi = U - 1;                    // last module whose first step <= step
@@ -192,7 +208,8 @@ __global__ __launch_bounds__(256) void k_query_planes(const float* __restrict__ 
   const int64_t sl = step - md.sbase;
   const int64_t q = grp * QB + qn;
   const int f = q < Q ? fq[(grp * U + lo) * QB + qn] : 0;
-  const int64_t c0 = 8 * (sb * sl + (sb / 2) * g + 16 * uc) + t;   // coordinate of byte 0
+  const int o = tiled ? 32 * g + 16 * uc : 32 * uc + 16 * g;
+  const int64_t c0 = 8 * (SB * sl + o) + t;                 // coordinate of byte 0
   const float* y = Y + q * ldy + md.coff;
   uint32_t hw[4] = {0u, 0u, 0u, 0u}, lw[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -205,72 +222,118 @@ __global__ __launch_bounds__(256) void k_query_planes(const float* __restrict__ 
     hw[jj >> 2] |= (uint32_t)(h & 0xFF) << (8 * (jj & 3));
     lw[jj >> 2] |= (uint32_t)(l & 0xFF) << (8 * (jj & 3));
   }
-  const int fr = 8 * uc + t;
-  int8_t* blk = planes + (gs * (sb / 4) + fr) * 1024;
+  int8_t* blk = planes + (gs * FRAGS + 8 * uc + t) * 1024;
   const int lane = qn + 32 * g;   // plane h; plane l is lane + 16
   *reinterpret_cast<uint4*>(blk + 16 * lane) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
   *reinterpret_cast<uint4*>(blk + 16 * (lane + 16)) = make_uint4(lw[0], lw[1], lw[2], lw[3]);
 }
 
-// Copies a store of n < 16 bytes into a zero-padded 16-byte slot.
-__global__ void k_pad16(const uint8_t* __restrict__ src, int n, uint8_t* __restrict__ dst) {
-  const int i = threadIdx.x;
-  dst[i] = i < n ? src[i] : (uint8_t)0;
-}
-
 // ---- candidate lists in LDS ---------------------------------------------------
-template <int CAP>
+template <int NQ, int CAP>
 struct Cand {
-  uint64_t key[QB][CAP];
-  uint32_t idx[QB][CAP];
-  int cnt[QB];
-  uint64_t thr[QB];
+  uint64_t key[NQ][CAP];
+  uint32_t idx[NQ][CAP];
+  int cnt[NQ];
+  uint64_t thr[NQ];
   int overflow;
 };
 
-// Sort a list (all NTH threads of the block; the first power of two of slots
-// that holds its entries, padded with empty ones), keep its first `topk`,
-// update the threshold. Entries past CAP (counted but not stored) are dropped here;
-// their owners insert them again.
-template <int CAP, int NTH>
-__device__ __forceinline__ void prune_list(uint64_t* key, uint32_t* idx, int* cnt, uint64_t* thr,
-                                           int topk) {
-  const int tid = threadIdx.x;
-  const int c = min(*cnt, CAP);
-  int P = 2;                     // sorted length: the least power of two >= c (CAP at most)
-  while (P < c) P <<= 1;
-  for (int i = c + tid; i < P; i += NTH) {
-    key[i] = 0ull;
-    idx[i] = 0xFFFFFFFFu;
-  }
-  __syncthreads();
-  for (int k = 2; k <= P; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = tid; i < P; i += NTH) {
-        const int p = i ^ j;
-        if (p > i) {
-          const uint64_t ka = key[i], kb = key[p];
-          const uint32_t ia = idx[i], ib = idx[p];
-          const bool desc = (i & k) == 0;
-          const bool ab = before(ka, ia, kb, ib);
-          if (desc ? !ab : ab) {
-            key[i] = kb; key[p] = ka;
-            idx[i] = ib; idx[p] = ia;
-          }
-        }
+// Selection over 64 PER entries held by one wave (empty slots: key 0, index
+// 0xFFFFFFFF), of which at least topk are not empty: the entries to keep,
+// exactly topk of them, are those with key > tk, or key == tk and idx <= ti. tk
+// is found bit by bit from the top: the largest value that at least topk keys
+// reach, stopping as soon as exactly topk do (then every key >= tk is kept).
+// Only ballots and scalar counts, no barrier: about 25 rounds for scores.
+template <int PER>
+__device__ __forceinline__ void wave_select(const uint64_t (&key)[PER], const uint32_t (&idx)[PER],
+                                            int topk, uint64_t& tk, uint32_t& ti) {
+  uint64_t t = 0;
+  for (int b = 63; b >= 0; --b) {
+    const uint64_t c = t | (1ull << b);
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) n += __popcll(__ballot(key[j] >= c));
+    if (n >= topk) {
+      t = c;
+      if (n == topk) {
+        tk = t;
+        ti = 0xFFFFFFFFu;
+        return;
       }
-      __syncthreads();
     }
   }
-  if (tid == 0) {
-    *thr = (c >= topk) ? key[topk - 1] : 0ull;
-    *cnt = c < topk ? c : topk;
+  // t is the topk-th key and more entries share it: the smallest indices win
+  int need = topk;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) need -= __popcll(__ballot(key[j] > t));
+  uint32_t v = 0;                            // the need-th smallest index among them
+  for (int b = 31; b >= 0; --b) {
+    const uint32_t c = v | (1u << b);
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) n += __popcll(__ballot(key[j] == t && idx[j] < c));
+    if (n < need) v = c;
   }
-  __syncthreads();
+  tk = t;
+  ti = v;
 }
-template <int CAP, int NTH>
-__device__ __forceinline__ void prune(Cand<CAP>& cd, int n, int topk) {
-  prune_list<CAP, NTH>(cd.key[n], cd.idx[n], &cd.cnt[n], &cd.thr[n], topk);
+
+// Writes the entries that wave_select keeps to key_o / idx_o (any order).
+template <int PER>
+__device__ __forceinline__ void wave_compact(const uint64_t (&key)[PER], const uint32_t (&idx)[PER],
+                                             uint64_t tk, uint32_t ti, uint64_t* key_o,
+                                             uint32_t* idx_o) {
+  int base = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const bool keep = key[j] > tk || (key[j] == tk && idx[j] <= ti);
+    const uint64_t m = __ballot(keep);
+    if (keep) {
+      const int at = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+      key_o[at] = key[j];
+      idx_o[at] = idx[j];
+    }
+    base += __popcll(m);
+  }
+}
+
+// One wave prunes one list to its topk entries (in any order) and sets its
+// threshold; a list of at most topk entries is left as it is. Entries past CAP
+// (counted but not stored) are dropped here; their owners insert them again.
+template <int CAP>
+__device__ __forceinline__ void prune_list(uint64_t* key, uint32_t* idx, int* cnt, uint64_t* thr,
+                                           int topk) {
+  constexpr int PER = CAP / 64;
+  const int lane = threadIdx.x & 63;
+  const int c = __builtin_amdgcn_readfirstlane(min(*cnt, CAP));
+  if (c < topk) {
+    if (lane == 0) *cnt = c;
+    return;
+  }
+  uint64_t k[PER];
+  uint32_t id[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int e = 64 * j + lane;
+    k[j] = e < c ? key[e] : 0ull;
+    id[j] = e < c ? idx[e] : 0xFFFFFFFFu;
+  }
+  uint64_t tk;
+  uint32_t ti;
+  wave_select<PER>(k, id, topk, tk, ti);
+  wave_compact<PER>(k, id, tk, ti, key, idx);
+  if (lane == 0) {
+    *cnt = topk;
+    *thr = tk;
+  }
+}
+// Prunes every list of at least `least` entries, NWV lists at a time. Callers
+// put a barrier before and after.
+template <int NQ, int CAP, int NWV>
+__device__ __forceinline__ void prune(Cand<NQ, CAP>& cd, int least, int topk) {
+  for (int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); q < NQ; q += NWV)
+    if (__builtin_amdgcn_readfirstlane(cd.cnt[q]) >= least)
+      prune_list<CAP>(cd.key[q], cd.idx[q], &cd.cnt[q], &cd.thr[q], topk);
 }
 
 constexpr int MAX_RNG = 64;   // module ranges of the multi-module pass
@@ -290,10 +353,10 @@ struct ScoreArgs {
   int64_t Q;
   int topk;
   float* full;
-  uint64_t* ckey;   // [grid][QB][topk]
+  uint64_t* ckey;   // [grid][NQ][topk], NQ = queries of the pass
   uint32_t* cidx;
   // multi-module pass: module ranges (range r = modules rng[r] .. rng[r+1]-1)
-  // and the per-(module, query, row) integer dots it writes, [U][QB][N]
+  // and the per-(module, query, row) integer dots it writes, [U][NQ][N]
   int n_rng;
   int32_t rng[MAX_RNG + 1];
   void* part;
@@ -306,34 +369,31 @@ __device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>,
   (f(std::integral_constant<int, I>{}), ...);
 }
 
-// Walks the steps of the modules in order (uniform, scalar registers).
-struct Cursor {
-  int u, sl, nst, kbytes, boff;
-};
-
-// NCLS: accumulator classes of the bit expansion (1, 2 or 4). D: steps
-// requested ahead. MODE 0: one module; its fp64 term is formed after the last
-// step and the rows are offered to the per-query candidate lists. MODE 1 / 2:
-// several modules; a work unit is (512-row block, range of modules), and at
-// the end of each module the exact dot <y_int, 2b - 1> of every (row, query)
-// is written to `part` as int32 (MODE 1, every k_u <= 2^16) or int64 (MODE 2);
-// k_score_fold then forms the fp64 terms and sums them in module order. CAP:
-// candidate slots per query (MODE 0). SB: bytes per row and step. RT: 32-row
-// tiles per wave (each plane fragment read from LDS feeds RT MFMAs). TILED:
-// the store is in the tiled layout (see eogp_sign_pack_tiled): each wave's
-// 32-row tile and step is one 2 KB block whose bytes are already in lane
-// order, read as two contiguous 1 KB loads; else rows are row-major.
-template <int NCLS, int D, int MODE, int CAP, int SB, int RT, bool TILED>
-__global__ __launch_bounds__(NTHR) void k_score(ScoreArgs a) {
-  constexpr bool MULTI = MODE != 0;
-  static_assert(!TILED || SB == 64, "the tiled layout has 64-byte row pieces per step");
+// NQT: groups of 16 queries per pass. RT: 32-row tiles per wave. NCLS:
+// accumulator classes of the bit expansion (1 or 2). MODE 0 / 3: one module (of
+// at most / more than 2^16 bits: its dots fit 32 bits or take 64); its fp64 term
+// is formed after the last step and the rows are offered to the per-query
+// candidate lists. MODE 1 / 2: several modules; a work unit is
+// (row block, range of modules), and at the end of each module the exact dot
+// <y_int, 2b - 1> of every (row, query) is written to `part` as int32 (MODE 1,
+// every k_u <= 2^16) or int64 (MODE 2); k_score_fold then forms the fp64 terms
+// and sums them in module order. CAP: candidate slots per query (MODE 0).
+// TILED: the store is in the tiled layout (see eogp_sign_pack_tiled): each
+// wave's 32-row tile and step is one 2 KB block whose bytes are already in
+// lane order, each half a contiguous 1 KB; else rows are row-major.
+template <int NQT, int RT, int NCLS, int MODE, int CAP, bool TILED>
+__global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_score(ScoreArgs a) {
+  constexpr bool MULTI = MODE == 1 || MODE == 2;
+  typedef typename std::conditional<MODE == 3, int64_t, int32_t>::type dot_t;   // one module's dots
+  constexpr int NQ = NQT * QB;
   constexpr int ROWS = NW * RT * 32;   // rows per block
-  static_assert(NCLS == 1 || NCLS == 2 || NCLS == 4, "bit-weight classes");
-  static_assert(D >= 2 && D <= 8, "ring depth");
-  using SS = StepShape<SB>;
-  constexpr int NU = SS::NU, FR = SS::FR, PU = SS::PU, PV = SS::PV;
-  __shared__ __attribute__((aligned(16))) uint4 sP[2][PU];
-  __shared__ Cand<MULTI ? 1 : CAP> cd;
+  static_assert(NCLS == 1 || NCLS == 2, "bit-weight classes");
+  static_assert(RT * NQT <= 8, "accumulator registers");
+  // fragments read ahead of their use, so that at least 8 MFMAs cover the LDS latency
+  constexpr int FD = RT * NQT >= 8 ? 1 : RT * NQT >= 4 ? 2 : 3;
+  __shared__ __attribute__((aligned(16))) uint4 sP[2][NQT * HALF_U4];
+  __shared__ Cand<MULTI ? 1 : NQ, MULTI ? 64 : CAP> cd;   // (unused by several modules)
   // the wave index through readfirstlane: wave-uniform for the compiler, so the
   // row and tile arithmetic that depends on it stays scalar
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -342,7 +402,7 @@ __global__ __launch_bounds__(NTHR) void k_score(ScoreArgs a) {
   const cptr<int32_t> cfq = (cptr<int32_t>)(a.fq);
   const cptr<int64_t> cys = (cptr<int64_t>)(a.ysum);
   if (!MULTI) {
-    if (tid < QB) {
+    if (tid < NQ) {
       cd.cnt[tid] = 0;
       cd.thr[tid] = 0ull;
     }
@@ -351,6 +411,9 @@ __global__ __launch_bounds__(NTHR) void k_score(ScoreArgs a) {
   }
   const int64_t n_blocks = (a.N + ROWS - 1) / ROWS;
   const uint32_t M1 = 0x01010101u;
+  int shv[8];                          // the shift of round t
+#pragma unroll
+  for (int t = 0; t < 8; ++t) shv[t] = opaque_shift(t - t % NCLS);
 
   // Work units. MODE 0: row blocks at a fixed stride. Multi-module: units
   // (range, block) in range-major order, dealt to the XCDs in contiguous
@@ -363,320 +426,361 @@ __global__ __launch_bounds__(NTHR) void k_score(ScoreArgs a) {
   const int nq = xq ? kXcds : 1, xcd = xq ? b % kXcds : 0;
   const int64_t chunk = (n_units + nq - 1) / nq;
   const int64_t q_end = std::min<int64_t>((int64_t)(xcd + 1) * chunk, n_units);
-  for (int64_t unit = (int64_t)xcd * chunk + b / nq; unit < q_end; unit += G / nq) {
+  const int64_t u_first = (int64_t)xcd * chunk + b / nq, u_step = G / nq;
+
+  // Where a walk over the steps of a unit stands (all uniform). n: steps of the
+  // unit; s: step within it; the rest (several modules, or row-major rows): the
+  // module, the step within it, its steps, bytes and first byte in a row.
+  struct Walk {
+    int64_t unit, blk;
+    int n, s, s_lo, u, u_hi, sl, nst, kbytes, boff;
+  };
+  auto open_module = [&](Walk& w) __attribute__((always_inline)) {
+    const int k = cmods[4 * w.u];
+    w.sl = 0;
+    w.nst = (k + 8 * SB - 1) / (8 * SB);
+    w.kbytes = k >> 3;
+    w.boff = cmods[4 * w.u + 2];
+  };
+  auto open_unit = [&](Walk& w, int64_t unit) __attribute__((always_inline)) {
+    w.unit = unit;
     const int rg = MULTI ? (int)(unit / n_blocks) : 0;
-    const int64_t blk = MULTI ? unit % n_blocks : unit;
-    const int u_lo = MULTI ? a.rng[rg] : 0;
-    const int u_hi = MULTI ? a.rng[rg + 1] : 1;
-    const int s_lo = MULTI ? cmods[4 * u_lo + 3] : 0;
-    const int s_hi = (MULTI && u_hi < a.U) ? cmods[4 * u_hi + 3] : a.n_steps;
-    const int n = s_hi - s_lo;
-    const uint4* pl_grp = a.planes + ((int64_t)a.grp * a.n_steps + s_lo) * PU;
-
-  auto start = [&](Cursor& c) __attribute__((always_inline)) {
-    const int k = cmods[4 * u_lo];
-    c.u = u_lo;
-    c.sl = 0;
-    c.nst = (k + 8 * SB - 1) / (8 * SB);
-    c.kbytes = k >> 3;
-    c.boff = cmods[4 * u_lo + 2];
+    w.blk = MULTI ? unit % n_blocks : unit;
+    w.u = MULTI ? a.rng[rg] : 0;
+    w.u_hi = MULTI ? a.rng[rg + 1] : 1;
+    w.s_lo = MULTI ? cmods[4 * w.u + 3] : 0;
+    w.n = ((MULTI && w.u_hi < a.U) ? cmods[4 * w.u_hi + 3] : a.n_steps) - w.s_lo;
+    w.s = 0;
+    if (MULTI || !TILED) open_module(w);
   };
-  auto advance = [&](Cursor& c) __attribute__((always_inline)) {
-    if (++c.sl == c.nst) {
-      c.sl = 0;
-      if (++c.u < u_hi) {
-        const int k = cmods[4 * c.u];
-        c.nst = (k + 8 * SB - 1) / (8 * SB);
-        c.kbytes = k >> 3;
-        c.boff = cmods[4 * c.u + 2];
-      }
-    }
+  auto next_step = [&](Walk& w) __attribute__((always_inline)) {   // within the unit
+    ++w.s;
+    if ((MULTI || !TILED) && ++w.sl == w.nst && ++w.u < w.u_hi) open_module(w);
   };
 
-    int64_t row[RT], rowc[RT];
-    const uint8_t* rowp[RT];
+  if (u_first < q_end) {
+    Walk wl, wc;   // the loads' walk and the products'
+    // this wave's rows in the loads' block: tiled, the tile's first block of
+    // the unit (uniform); row-major, this lane's row
+    const uint8_t* lrow[RT];
+    auto row_of = [&](int64_t blk, int rt) { return blk * ROWS + (int64_t)(wid * RT + rt) * 32 + r32; };
+    auto load_unit = [&](int64_t unit) __attribute__((always_inline)) {
+      open_unit(wl, unit);
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      row[rt] = blk * ROWS + (int64_t)(wid * RT + rt) * 32 + r32;   // this lane's stored row
-      rowc[rt] = std::min<int64_t>(row[rt], a.N - 1);                // rows past N: never reported
-      if constexpr (TILED) {
-        const int64_t tile = std::min<int64_t>(blk * (ROWS / 32) + wid * RT + rt, a.n_tiles - 1);
-        rowp[rt] = a.codes + tile * (int64_t)a.n_steps * 2048 + lane * 16;
-      } else {
-        rowp[rt] = a.codes + rowc[rt] * a.cstride + (SB / 2) * hg;
-      }
-    }
-
-    i32x16 acc[RT][NCLS];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int w = 0; w < NCLS; ++w)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[rt][w][r] = 0;
-    double sc[MULTI ? 1 : RT][8];   // [tile][i]: query 8 (i / 4) + 4 (lane / 32) + i % 4 of the group
-
-    // ring slot: [rt][0, NU) the lane's code words of tile rt, [RT][0, PV)
-    // the thread's share of the step's plane fragments
-    constexpr int RW = NU > PV ? NU : PV;
-    uint4 ring[D][RT + 1][RW];
-    uint32_t s16[RT];      // one module: the rows' scales, requested before the codes
-    if (!MULTI) {
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) s16[rt] = a.scales[rowc[rt]];
-    }
-    Cursor cc, cl;
-    start(cc);
-    start(cl);
-
-    // plane fragments and code words of step `target` (the load cursor's)
-    // into ring slot SL, D steps ahead. Every step issues the same loads in
-    // the order they are consumed, so the in-order load counter never makes
-    // a step wait for a later step's data, and the number of requests in
-    // flight never depends on the step or the lane. In a partial step (the
-    // last of a module whose k is not a multiple of 8 SB, or a step past the
-    // end) a lane whose 16 bytes are not all inside the module reads 16
-    // readable bytes instead: the 8 bytes before its 8 valid ones (the valid
-    // half is then the upper one), or the store's first 16 bytes; `fixup`
-    // keeps the valid bytes when the step is used.
-    int64_t voff[D];
-    int vbytes[D];
-    auto load_step = [&](auto slot_c, int target) __attribute__((always_inline)) {
-      constexpr int SL = decltype(slot_c)::value;
-      const bool live = target < n;
-      const uint4* psrc = pl_grp + (int64_t)(live ? target : n - 1) * PU + tid;
-#pragma unroll
-      for (int v = 0; v < PV; ++v) ring[SL][RT][v] = psrc[v * NTHR];
-      if constexpr (TILED) {
-        // every step of a module is whole (k_u a multiple of 512); a step
-        // past the range reads the range's last block again, unused
-        const int64_t so = (int64_t)(s_lo + (live ? target : n - 1)) * 2048;
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-          for (int uc = 0; uc < NU; ++uc)
-            ring[SL][rt][uc] = *reinterpret_cast<const uint4*>(rowp[rt] + so + uc * 1024);
-        voff[SL] = 0;
-        vbytes[SL] = SB;
-        return;
-      }
-      const int64_t off = (int64_t)cl.boff + SB * cl.sl;
-      const int valid = live ? min(SB, cl.kbytes - SB * cl.sl) : 0;   // multiple of 8
-      voff[SL] = off;
-      vbytes[SL] = valid;
-      if (valid == SB) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-          for (int uc = 0; uc < NU; ++uc)
-            ring[SL][rt][uc] = *reinterpret_cast<const uint4*>(rowp[rt] + off + 16 * uc);
-      } else {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-          for (int uc = 0; uc < NU; ++uc) {
-            const int have = valid - (SB / 2) * hg - 16 * uc;
-            const int64_t pos = off + (SB / 2) * hg + 16 * uc;   // within the row
-            const bool at0 = rowc[rt] == 0 && pos == 0;          // the store's first byte
-            const uint8_t* src = rowp[rt] + off + 16 * uc;
-            const uint8_t* p = have >= 16 ? src : (have >= 8 && !at0) ? src - 8 : a.codes;
-            ring[SL][rt][uc] = *reinterpret_cast<const uint4*>(p);
-          }
+      for (int rt = 0; rt < RT; ++rt) {
+        if constexpr (TILED) {
+          const int64_t tile = std::min<int64_t>(wl.blk * (ROWS / 32) + wid * RT + rt, a.n_tiles - 1);
+          const uint64_t off = (uint64_t)((tile * a.n_steps + wl.s_lo) * 2048);
+          lrow[rt] = a.codes + (((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(off >> 32)) << 32) |
+                                (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)off));
+        } else {
+          lrow[rt] = a.codes + std::min<int64_t>(row_of(wl.blk, rt), a.N - 1) * a.cstride;
+        }
       }
     };
-    // keeps the valid bytes of a partial step (branch-free selects)
-    auto fixup = [&](auto slot_c) __attribute__((always_inline)) {
-      constexpr int SL = decltype(slot_c)::value;
+
+    i32x16 acc[RT][NQT][NCLS];
+    auto clear_acc = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int uc = 0; uc < NU; ++uc) {
-          const int have = vbytes[SL] - (SB / 2) * hg - 16 * uc;
-          const bool at0 = rowc[rt] == 0 && voff[SL] + (SB / 2) * hg + 16 * uc == 0;
-          const uint4 v = ring[SL][rt][uc];
-          const uint32_t full = have >= 16 ? ~0u : 0u;
-          const uint32_t half = (have >= 8 && have < 16) ? ~0u : 0u;
-          const uint32_t lo0 = at0 ? v.x : v.z, lo1 = at0 ? v.y : v.w;
-          ring[SL][rt][uc] = make_uint4((v.x & full) | (lo0 & half), (v.y & full) | (lo1 & half),
-                                        v.z & full, v.w & full);
+        for (int qt = 0; qt < NQT; ++qt)
+#pragma unroll
+          for (int w = 0; w < NCLS; ++w)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[rt][qt][w][r] = 0;
+    };
+    clear_acc();
+    uint4 cw[2][RT];      // code words of the two halves, requested one step ahead
+    i32x4 pw[NQT];        // this thread's share of the next half's plane fragments
+    uint32_t s16[RT];     // one module: the rows' scales
+
+    // Half H of the loads' step: the plane fragments (staged at the end of the
+    // next half) before the code words (used after it), in the order they are
+    // consumed, as the load counter completes in order. Row-major rows whose
+    // module ends inside the half (k_u a multiple of 64 bits): each lane reads
+    // its 16 bytes as two pieces of 8, those outside the module from readable
+    // bytes instead (the first piece, or the store's first 8 bytes): the planes
+    // are zero there, so the loaded words are used as they are. (Masked under a
+    // branch before their use, some variants' shifts overwrote words still
+    // needed; tests/test_gpu_score_passes.py covers every variant.)
+    auto load_half = [&](auto half_c) __attribute__((always_inline)) {
+      constexpr int H = decltype(half_c)::value;
+#pragma unroll
+      for (int qt = 0; qt < NQT; ++qt)
+        pw[qt] = reinterpret_cast<const i32x4*>(
+            a.planes)[((((int64_t)a.grp + qt) * a.n_steps + wl.s_lo + wl.s) * FRAGS + 8 * H) * 64 + tid];
+      if constexpr (TILED) {
+        const int64_t so = (int64_t)wl.s * 2048 + H * 1024;
+        const uint32_t lo = (uint32_t)lane * 16;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) cw[H][rt] = *reinterpret_cast<const uint4*>(lrow[rt] + so + lo);
+      } else {
+        const int at = SB * wl.sl + 32 * H + 16 * hg;           // within the module's bytes
+        const int64_t pos = (int64_t)wl.boff + at;              // within the row
+        if (SB * wl.sl + 32 * H + 32 <= wl.kbytes) {            // uniform
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) cw[H][rt] = *reinterpret_cast<const uint4*>(lrow[rt] + pos);
+        } else {
+          const int have = wl.kbytes - at;                      // multiple of 8
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            const uint8_t* p0 = have >= 8 ? lrow[rt] + pos : a.codes;
+            const uint8_t* p1 = have >= 16 ? lrow[rt] + pos + 8 : p0;
+            const uint2 v0 = *reinterpret_cast<const uint2*>(p0), v1 = *reinterpret_cast<const uint2*>(p1);
+            cw[H][rt] = make_uint4(v0.x, v0.y, v1.x, v1.y);
+          }
         }
+      }
+    };
+    auto stage = [&](auto half_c) __attribute__((always_inline)) {
+      constexpr int H = decltype(half_c)::value;
+#pragma unroll
+      for (int qt = 0; qt < NQT; ++qt) *reinterpret_cast<i32x4*>(&sP[H][qt * HALF_U4 + tid]) = pw[qt];
+    };
+    // the loads' walk moves on, into the next unit after the last step of this
+    // one (past the last unit it stays, and its last step is read again, unused)
+    auto advance_loads = [&]() __attribute__((always_inline)) {
+      if (wl.s + 1 < wl.n) next_step(wl);
+      else if (wl.unit + u_step < q_end) load_unit(wl.unit + u_step);
     };
 
-    // end of module u: the exact dot n = 2 n1 - sum y_int of every (row,
-    // query); one module: its term s * n * 2^-f; several: n to `part`
-    auto fold = [&](int u) __attribute__((always_inline)) {
-      const int64_t mo = (a.grp * a.U + u) * QB;
+    // n1 of (tile rt, group qt, query i of the lane's eight) from the classes
+    auto class_sum = [&](int rt, int qt, int r) __attribute__((always_inline)) {
+      int v = acc[rt][qt][0][r];
+      if constexpr (NCLS == 2) v += acc[rt][qt][1][r] >> 1;
+      return v;
+    };
+    // <y_int, 2b - 1> of (row, query): query 8 (i / 4) + 4 hg + i % 4 of group qt
+    auto dot = [&](int rt, int qt, int i, int64_t ys) __attribute__((always_inline)) -> int64_t {
+      const int64_t n1 = 256 * (int64_t)class_sum(rt, qt, i) + (int64_t)class_sum(rt, qt, i + 8);
+      return 2 * n1 - ys;
+    };
+    auto fold_module = [&]() __attribute__((always_inline)) {   // several modules: dots to `part`
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        int H[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          int v = acc[rt][0][r];
-#pragma unroll
-          for (int w = 1; w < NCLS; ++w) v += acc[rt][w][r] >> w;
-          H[r] = v;
-        }
+      for (int qt = 0; qt < NQT; ++qt) {
+        const int64_t mo = ((a.grp + qt) * a.U + wc.u) * QB;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const int i0 = 8 * (i >> 2) + (i & 3);
           const int64_t ys = hg ? cys[mo + i0 + 4] : cys[mo + i0];
-          const int64_t n1 = 256 * (int64_t)H[i] + (int64_t)H[i + 8];
-          const int64_t nn = 2 * n1 - ys;
-          if constexpr (MULTI) {
-            if (row[rt] < a.N) {
-              const int64_t o = ((int64_t)u * QB + i0 + 4 * hg) * a.N + row[rt];
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            const int64_t row = row_of(wc.blk, rt), nn = dot(rt, qt, i, ys);
+            if (row < a.N) {
+              const int64_t o = ((int64_t)wc.u * NQ + QB * qt + i0 + 4 * hg) * a.N + row;
               if constexpr (MODE == 1) static_cast<int32_t*>(a.part)[o] = (int32_t)nn;
               else static_cast<int64_t*>(a.part)[o] = nn;
             }
-          } else {
-            const int f = hg ? cfq[mo + i0 + 4] : cfq[mo + i0];
-            const double sv = (double)f16_bits_to_f32((uint16_t)s16[rt]);
-            sc[rt][i] = ldexp(sv * (double)nn, -f);
           }
         }
-#pragma unroll
-        for (int w = 0; w < NCLS; ++w)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[rt][w][r] = 0;
       }
+      clear_acc();
     };
 
-    auto step = [&](auto slot_c, int s) __attribute__((always_inline)) {
-      constexpr int SL = decltype(slot_c)::value;
-      constexpr int NX = (SL + 1) % D;   // slot of step s + 1
-      const int buf = s & 1;
-      if (vbytes[SL] < SB) fixup(slot_c);
-      // fragment f = 8 uc + t of the step, read from LDS two rounds ahead of
-      // its use so the LDS latency stays hidden; each feeds the RT tiles
-      const uint4* frag = &sP[buf][lane];
-      i32x4 fr[3];
-      fr[0] = __builtin_bit_cast(i32x4, frag[0]);
-      fr[1] = __builtin_bit_cast(i32x4, frag[64]);
+    auto half_step = [&](auto half_c) __attribute__((always_inline)) {
+      constexpr int H = decltype(half_c)::value;
+      const uint4* frag = &sP[H][lane];
+      i32x4 fr[FD + 1][NQT];
 #pragma unroll
-      for (int f = 0; f < FR; ++f) {
-        if (f + 2 < FR) fr[(f + 2) % 3] = __builtin_bit_cast(i32x4, frag[(f + 2) * 64]);
-        const int uc = f >> 3, t = f & 7;
+      for (int f = 0; f < FD; ++f)
+#pragma unroll
+        for (int qt = 0; qt < NQT; ++qt) fr[f][qt] = __builtin_bit_cast(i32x4, frag[qt * HALF_U4 + f * 64]);
+      __builtin_amdgcn_sched_group_barrier(0x100, FD * NQT, 0);                // the first DS reads
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        if (t + FD < 8)
+#pragma unroll
+          for (int qt = 0; qt < NQT; ++qt)
+            fr[(t + FD) % (FD + 1)][qt] = __builtin_bit_cast(i32x4, frag[qt * HALF_U4 + (t + FD) * 64]);
         const int w = t % NCLS, sh = t - w;
         const uint32_t mk = M1 << w;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          const uint4 c = ring[SL][rt][uc];
+          const uint4 c = cw[H][rt];
           // bits shifted across the halves land at 32 - sh and above, never
           // under the mask (its highest bit is 24 + w, and sh + w <= 7)
           uint64_t p0 = ((uint64_t)c.y << 32) | c.x, p1 = ((uint64_t)c.w << 32) | c.z;
           if (sh) {
-            p0 = shr_pair(p0, sh);
-            p1 = shr_pair(p1, sh);
+            p0 >>= shv[t];
+            p1 >>= shv[t];
           }
           i32x4 av;
           av[0] = (int)((uint32_t)p0 & mk);
           av[1] = (int)((uint32_t)(p0 >> 32) & mk);
           av[2] = (int)((uint32_t)p1 & mk);
           av[3] = (int)((uint32_t)(p1 >> 32) & mk);
-          acc[rt][w] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[f % 3], av, acc[rt][w], 0, 0, 0);
+#pragma unroll
+          for (int qt = 0; qt < NQT; ++qt)
+            acc[rt][qt][w] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[t % (FD + 1)][qt], av, acc[rt][qt][w], 0, 0, 0);
         }
-        // per round: the read two rounds ahead, then each tile's expansion and MFMA
-        if (f + 2 < FR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // DS read
+        // per round: the fragment reads ahead, then each tile's expansion and MFMAs
+        if (t + FD < 8) __builtin_amdgcn_sched_group_barrier(0x100, NQT, 0);   // DS read
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          __builtin_amdgcn_sched_group_barrier(0x002, NCLS == 1 ? 8 : NCLS == 2 ? 6 : 5, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                 // MFMA
+          __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);                   // VALU
+          __builtin_amdgcn_sched_group_barrier(0x008, NQT, 0);                 // MFMA
         }
       }
-      if (MULTI) {
-        if (cc.sl == cc.nst - 1) fold(cc.u);
-        advance(cc);
-      }
-      load_step(slot_c, s + D);
-      advance(cl);
-#pragma unroll
-      for (int v = 0; v < PV; ++v) sP[buf ^ 1][tid + v * NTHR] = ring[NX][RT][v];
-      __syncthreads();
     };
+    constexpr std::integral_constant<int, 0> H0{};
+    constexpr std::integral_constant<int, 1> H1{};
 
-    // prologue: the first D steps requested, step 0's planes staged
-    for_each_index(std::make_integer_sequence<int, D>{}, [&](auto i_c) __attribute__((always_inline)) {
-      load_step(i_c, decltype(i_c)::value);
-      advance(cl);
-    });
-#pragma unroll
-    for (int v = 0; v < PV; ++v) sP[0][tid + v * NTHR] = ring[0][RT][v];
+    // prologue: step 0 requested, its first half staged
+    load_unit(u_first);
+    load_half(H0);
+    stage(H0);
+    load_half(H1);
+    advance_loads();
     __syncthreads();
-    // whole rounds of D steps (every step of a round runs, so the loads in
-    // flight are the same on every path around the loop), then the rest
-    int s0 = 0;
-    for (; s0 + D <= n; s0 += D) {
-      for_each_index(std::make_integer_sequence<int, D>{}, [&](auto i_c) __attribute__((always_inline)) {
-        step(i_c, s0 + decltype(i_c)::value);
-      });
-    }
-    for_each_index(std::make_integer_sequence<int, D - 1>{}, [&](auto i_c) __attribute__((always_inline)) {
-      if (s0 + decltype(i_c)::value < n) step(i_c, s0 + decltype(i_c)::value);
-    });
-
-    if constexpr (!MULTI) {
-      fold(0);
-
-      // candidates of this block; a full list is pruned and the entries that
-      // did not fit are offered again (the loop condition is uniform). The
-      // opaque copy of the lane half keeps the list addresses from being
-      // computed once before the block loop and held through it.
-      int hq = hg;
-      asm volatile("" : "+v"(hq));
-      auto qsel = [&](int i) { return 8 * (i >> 2) + 4 * hq + (i & 3); };
-      uint32_t pend = 0;
-  #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-  #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int64_t q = a.grp * QB + qsel(i);
-          if (row[rt] < a.N && q < a.Q) {
-            if (a.full) a.full[q * a.N + row[rt]] = (float)sc[rt][i];
-            pend |= 1u << (8 * rt + i);
-          }
-        }
-      for (;;) {
-  #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-  #pragma unroll
+    for (int64_t unit = u_first; unit < q_end; unit += u_step) {
+      open_unit(wc, unit);
+      if (!MULTI) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) s16[rt] = a.scales[std::min<int64_t>(row_of(wc.blk, rt), a.N - 1)];
+      }
+      for (int s = 0; s < wc.n; ++s) {
+        half_step(H0);
+        stage(H1);
+        load_half(H0);
+        __syncthreads();
+        half_step(H1);
+        if (MULTI && wc.sl == wc.nst - 1) fold_module();
+        stage(H0);                     // the next step's (or the next unit's first) half
+        load_half(H1);
+        __syncthreads();
+        next_step(wc);
+        advance_loads();
+      }
+      if constexpr (!MULTI) {
+        // candidates of this block. The opaque copy of the lane half keeps the
+        // list addresses from being computed once before the block loop and
+        // held through it.
+        int hq = hg;
+        asm volatile("" : "+v"(hq));
+        // the exact dots take the accumulators' place (half their registers)
+        dot_t nd[RT][NQT][8];
+#pragma unroll
+        for (int qt = 0; qt < NQT; ++qt)
+#pragma unroll
           for (int i = 0; i < 8; ++i) {
-            const uint32_t bit = 1u << (8 * rt + i);
-            if (pend & bit) {
-              const int qn = qsel(i);
-              const uint64_t key = order_key(sc[rt][i]);
-              if (key < cd.thr[qn]) {
-                pend &= ~bit;
-              } else {
-                const int pos = atomicAdd(&cd.cnt[qn], 1);
-                if (pos < CAP) {
-                  cd.key[qn][pos] = key;
-                  cd.idx[qn][pos] = (uint32_t)row[rt];
+            const int64_t mo = (a.grp + qt) * QB + 8 * (i >> 2) + (i & 3);
+            const int64_t ys = hq ? cys[mo + 4] : cys[mo];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) nd[rt][qt][i] = (dot_t)dot(rt, qt, i, ys);
+          }
+        // f(qt, i, list, exponent) for the lane's queries. The dots pass through
+        // an opaque step first: each walk forms its scores anew instead of
+        // keeping them (two registers each) from one walk to the next.
+        auto each_query = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+          for (int qt = 0; qt < NQT; ++qt)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              const int i0 = 8 * (i >> 2) + (i & 3);
+              const int64_t mo = (a.grp + qt) * QB + i0;
+              const int fx = hq ? cfq[mo + 4] : cfq[mo];
+#pragma unroll
+              for (int rt = 0; rt < RT; ++rt) asm volatile("" : "+v"(nd[rt][qt][i]));
+              f(qt, i, QB * qt + i0 + 4 * hq, fx);
+            }
+        };
+        auto score = [&](int rt, int qt, int i, int f) __attribute__((always_inline)) {
+          const double sv = (double)f16_bits_to_f32((uint16_t)s16[rt]);
+          return ldexp(sv * (double)nd[rt][qt][i], -f);
+        };
+        uint64_t pend = 0;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          if (row_of(wc.blk, rt) < a.N)
+            for (int e = 0; e < 8 * NQT; ++e) pend |= 1ull << (8 * NQT * rt + e);
+        if (unit == u_first) {
+          // first block: the threshold from the lanes' maxima (256 rows' worth)
+          each_query([&](int qt, int i, int qn, int fx) __attribute__((always_inline)) {
+            uint64_t m = 0;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+              const uint64_t key = order_key(score(rt, qt, i, fx));
+              if ((pend >> (8 * NQT * rt)) & 1) m = key > m ? key : m;
+            }
+            cd.key[qn][wid * 32 + r32] = m;
+          });
+          __syncthreads();
+          for (int q = wid; q < NQ; q += NW) {
+            uint64_t m[4];
+            uint32_t id[4];
+            int have = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              m[j] = cd.key[q][64 * j + lane];
+              id[j] = 0;
+              have += __popcll(__ballot(m[j] != 0));
+            }
+            if (have >= a.topk) {
+              uint64_t tk;
+              uint32_t ti;
+              wave_select<4>(m, id, a.topk, tk, ti);
+              if (lane == 0) cd.thr[q] = tk;
+            }
+          }
+          __syncthreads();
+        }
+        if (a.full)
+          each_query([&](int qt, int i, int qn, int fx) __attribute__((always_inline)) {
+            const int64_t q = a.grp * QB + qn;
+            if (q < a.Q)
+#pragma unroll
+              for (int rt = 0; rt < RT; ++rt) {
+                const int64_t row = row_of(wc.blk, rt);
+                if (row < a.N) a.full[q * a.N + row] = (float)score(rt, qt, i, fx);
+              }
+          });
+        // a full list is pruned and the entries that did not fit are offered
+        // again (the loop condition is uniform)
+        for (;;) {
+          each_query([&](int qt, int i, int qn, int fx) __attribute__((always_inline)) {
+            const uint64_t thr = cd.thr[qn];
+            const bool live = a.grp * QB + qn < a.Q;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+              const uint64_t bit = 1ull << (8 * NQT * rt + 8 * qt + i);
+              if (live && (pend & bit)) {
+                const uint64_t key = order_key(score(rt, qt, i, fx));
+                if (key < thr) {
                   pend &= ~bit;
                 } else {
-                  cd.overflow = 1;
+                  const int pos = atomicAdd(&cd.cnt[qn], 1);
+                  if (pos < CAP) {
+                    cd.key[qn][pos] = key;
+                    cd.idx[qn][pos] = (uint32_t)row_of(wc.blk, rt);
+                    pend &= ~bit;
+                  } else {
+                    cd.overflow = 1;
+                  }
                 }
               }
             }
-          }
-        __syncthreads();
-        const int ov = cd.overflow;
-        __syncthreads();
-        if (!ov) break;
-        for (int qq = 0; qq < QB; ++qq)
-          if (cd.cnt[qq] >= CAP) prune<CAP, NTHR>(cd, qq, a.topk);
-        if (tid == 0) cd.overflow = 0;
-        __syncthreads();
+          });
+          __syncthreads();
+          const int ov = cd.overflow;
+          __syncthreads();
+          if (!ov) break;
+          prune<NQ, CAP, NW>(cd, CAP, a.topk);
+          if (tid == 0) cd.overflow = 0;
+          __syncthreads();
+        }
+        clear_acc();
       }
     }
   }
   if constexpr (!MULTI) {
-    // lists of at most topk entries are written as they are (the merge
-    // takes candidates in any order)
-    for (int qq = 0; qq < QB; ++qq)
-      if (cd.cnt[qq] > a.topk) prune<CAP, NTHR>(cd, qq, a.topk);
-    for (int i = tid; i < QB * a.topk; i += NTHR) {
+    // (the merge takes candidates in any order)
+    __syncthreads();
+    prune<NQ, CAP, NW>(cd, a.topk + 1, a.topk);
+    __syncthreads();
+    for (int i = tid; i < NQ * a.topk; i += NTHR) {
       const int qq = i / a.topk, e = i % a.topk;
-      const int64_t o = ((int64_t)blockIdx.x * QB + qq) * a.topk + e;
+      const int64_t o = ((int64_t)blockIdx.x * NQ + qq) * a.topk + e;
       const bool have = e < cd.cnt[qq];
       a.ckey[o] = have ? cd.key[qq][e] : 0ull;
       a.cidx[o] = have ? cd.idx[qq][e] : 0xFFFFFFFFu;
@@ -688,18 +792,20 @@ __global__ __launch_bounds__(NTHR) void k_score(ScoreArgs a) {
 // takes queries 4w .. 4w+3 of the group for 64 consecutive stored rows (one
 // per lane); for u = 0 .. U-1 in order, score += s_{i,u} * n * 2^-f (each
 // term exact in fp64), then the rows are offered to the per-query candidate
-// lists as in k_score. Workgroups walk blocks of 64 rows at a fixed stride.
+// lists as in k_score. Workgroups walk blocks of 64 rows at a fixed stride;
+// grid.y: the groups of 16 queries of the pass.
 struct FoldArgs {
-  const void* part;           // [U][QB][N] int32 or int64
+  const void* part;           // [U][NQ][N] int32 or int64
   const uint16_t* scales;     // [N][U] fp16 bits
   int64_t N;
   int U;
   const int32_t* fq;          // [groups][U][16]
-  int64_t grp;
+  int64_t grp;                // first group of 16 queries of the pass; group grp + blockIdx.y here
+  int nq;                     // NQ: queries of the pass
   int64_t Q;
   int topk;
   float* full;
-  uint64_t* ckey;             // [grid][QB][topk]
+  uint64_t* ckey;             // [grid.x][NQ][topk]
   uint32_t* cidx;
 };
 constexpr int FOLD_THR = 256;
@@ -708,9 +814,10 @@ constexpr int FOLD_QW = QB / (FOLD_THR / 64);   // queries per wave
 
 template <int CAP, bool N64>
 __global__ __launch_bounds__(FOLD_THR) void k_score_fold(FoldArgs a) {
-  __shared__ Cand<CAP> cd;
+  __shared__ Cand<QB, CAP> cd;
   const int tid = threadIdx.x, lane = tid & 63;
   const int q0 = __builtin_amdgcn_readfirstlane((tid >> 6) * FOLD_QW);   // wave-uniform
+  const int64_t grp = a.grp + blockIdx.y;
   const cptr<int32_t> cfq = (cptr<int32_t>)(a.fq);
   if (tid < QB) {
     cd.cnt[tid] = 0;
@@ -731,10 +838,10 @@ __global__ __launch_bounds__(FOLD_THR) void k_score_fold(FoldArgs a) {
 #pragma unroll 4
     for (int u = 0; u < a.U; ++u) {
       const double sv = (double)f16_bits_to_f32(a.scales[rowc * a.U + u]);
-      const int64_t mo = (a.grp * a.U + u) * QB + q0;
+      const int64_t mo = (grp * a.U + u) * QB + q0;
 #pragma unroll
       for (int j = 0; j < FOLD_QW; ++j) {
-        const int64_t o = ((int64_t)u * QB + q0 + j) * a.N + rowc;
+        const int64_t o = ((int64_t)u * a.nq + blockIdx.y * QB + q0 + j) * a.N + rowc;
         const int64_t nn = N64 ? p64[o] : (int64_t)p32[o];
         sc[j] += ldexp(sv * (double)nn, -cfq[mo + j]);
       }
@@ -742,7 +849,7 @@ __global__ __launch_bounds__(FOLD_THR) void k_score_fold(FoldArgs a) {
     uint32_t pend = 0;
 #pragma unroll
     for (int j = 0; j < FOLD_QW; ++j) {
-      const int64_t qg = a.grp * QB + q0 + j;
+      const int64_t qg = grp * QB + q0 + j;
       if (ok && qg < a.Q) {
         if (a.full) a.full[qg * a.N + row] = (float)sc[j];
         pend |= 1u << j;
@@ -773,178 +880,273 @@ __global__ __launch_bounds__(FOLD_THR) void k_score_fold(FoldArgs a) {
       const int ov = cd.overflow;
       __syncthreads();
       if (!ov) break;
-      for (int qq = 0; qq < QB; ++qq)
-        if (cd.cnt[qq] >= CAP) prune<CAP, FOLD_THR>(cd, qq, a.topk);
+      prune<QB, CAP, FOLD_THR / 64>(cd, CAP, a.topk);
       if (tid == 0) cd.overflow = 0;
       __syncthreads();
     }
   }
-  for (int qq = 0; qq < QB; ++qq)
-    if (cd.cnt[qq] > a.topk) prune<CAP, FOLD_THR>(cd, qq, a.topk);
+  __syncthreads();
+  prune<QB, CAP, FOLD_THR / 64>(cd, a.topk + 1, a.topk);
+  __syncthreads();
   for (int i = tid; i < QB * a.topk; i += FOLD_THR) {
     const int qq = i / a.topk, e = i % a.topk;
-    const int64_t o = ((int64_t)blockIdx.x * QB + qq) * a.topk + e;
+    const int64_t o = ((int64_t)blockIdx.x * a.nq + blockIdx.y * QB + qq) * a.topk + e;
     const bool have = e < cd.cnt[qq];
     a.ckey[o] = have ? cd.key[qq][e] : 0ull;
     a.cidx[o] = have ? cd.idx[qq][e] : 0xFFFFFFFFu;
   }
 }
 
-// Reduction of the per-workgroup candidate lists ([G][QB][topk] keys and
+// Reduction of the per-workgroup candidate lists ([G][NQ][topk] keys and
 // indices, empty slots marked by index 0xFFFFFFFF) in two levels: workgroup
-// (n, sp) merges lists sp * per .. sp * per + per - 1 of query n of the group
+// (n, sp) merges lists sp * per .. sp * per + per - 1 of query n of the pass
 // into one list of the same form (!FINAL, list sp of the output), then one
-// workgroup per query merges those into the sorted top-k (FINAL). Each round
-// requests MRU candidates per thread before any is used; a list longer than
-// MCAP - 256 MRU is pruned before the next round, so a round always fits.
+// workgroup per query merges those into the sorted top-k (FINAL). Each of the
+// four waves selects the top-k of its share, up to 512 entries at a time in
+// registers (wave_select), then the first wave selects among the four: no
+// barrier but one between the two. Only the final top-k is sorted. (Before, a
+// bitonic sort of up to 1,024 entries by the whole workgroup per 512 entries,
+// one barrier per exchange stage: 49 + 46 us for the two levels at 256 lists of
+// 100 for 16 queries, now 21 + 25 us for 32.)
+constexpr int MRG_THR = 256, MRG_W = MRG_THR / 64, MRG_PER = 8;
 struct MergeList {
-  uint64_t key[MCAP];
-  uint32_t idx[MCAP];
-  int cnt;
-  uint64_t thr;
+  uint64_t key[MRG_W][MAX_TOPK];
+  uint32_t idx[MRG_W][MAX_TOPK];
+  int cnt[MRG_W];
 };
+// One wave: the top-k of the `total` entries that get(e, key, idx) yields
+// (empty ones have index 0xFFFFFFFF) into key_o / idx_o; returns their number.
+// key_o / idx_o may be read by get only at the same or a later entry than
+// those already taken.
+template <typename Get>
+__device__ __forceinline__ int wave_topk(int64_t total, int topk, uint64_t* key_o, uint32_t* idx_o,
+                                         int kept, Get&& get) {
+  const int lane = threadIdx.x & 63;
+  for (int64_t pos = 0; pos < total; pos += 64 * MRG_PER - kept) {
+    // slots 0 .. kept - 1: the entries kept so far; then entries pos ..
+    uint64_t key[MRG_PER];
+    uint32_t id[MRG_PER];
+    int have = 0;
+#pragma unroll
+    for (int j = 0; j < MRG_PER; ++j) {
+      const int slot = 64 * j + lane;
+      key[j] = 0ull;
+      id[j] = 0xFFFFFFFFu;
+      if (slot < kept) {
+        key[j] = key_o[slot];
+        id[j] = idx_o[slot];
+      } else if (pos + slot - kept < total) {
+        get(pos + slot - kept, key[j], id[j]);
+      }
+      have += __popcll(__ballot(id[j] != 0xFFFFFFFFu));
+    }
+    const int before_kept = kept;
+    uint64_t tk = 0;
+    uint32_t ti = 0xFFFFFFFEu;               // every entry that is not empty
+    if (have > topk) wave_select<MRG_PER>(key, id, topk, tk, ti);
+    wave_compact<MRG_PER>(key, id, tk, ti, key_o, idx_o);
+    kept = have < topk ? have : topk;
+    pos += kept - before_kept;               // the loop adds 512 less the new count
+  }
+  return kept;
+}
 template <bool FINAL>
-__global__ __launch_bounds__(256, 1) void k_merge(const uint64_t* __restrict__ ckey,
-                                                  const uint32_t* __restrict__ cidx, int G, int per,
-                                                  int64_t grp, int64_t Q, int topk,
-                                                  int64_t* __restrict__ out_idx,
-                                                  float* __restrict__ out_score,
-                                                  uint64_t* __restrict__ okey,
-                                                  uint32_t* __restrict__ oidx) {
+__global__ __launch_bounds__(MRG_THR, 1) void k_merge(const uint64_t* __restrict__ ckey,
+                                                      const uint32_t* __restrict__ cidx, int G,
+                                                      int per, int nq, int64_t grp, int64_t Q,
+                                                      int topk, int64_t* __restrict__ out_idx,
+                                                      float* __restrict__ out_score,
+                                                      uint64_t* __restrict__ okey,
+                                                      uint32_t* __restrict__ oidx) {
   __shared__ MergeList ml;
   const int n = blockIdx.x, sp = blockIdx.y;
   const int64_t q = grp * QB + n;
   if (q >= Q) return;                         // never read by the next level either
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    ml.cnt = 0;
-    ml.thr = 0ull;
+  const int tid = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l0 = sp * per, l1 = std::min(G, l0 + per);
+  const int pw = (l1 - l0 + MRG_W - 1) / MRG_W;             // lists of this workgroup's waves
+  const int w0 = std::min(l1, l0 + wid * pw), w1 = std::min(l1, w0 + pw);
+  const int mine = wave_topk((int64_t)(w1 - w0) * topk, topk, ml.key[wid], ml.idx[wid], 0,
+                             [&](int64_t e, uint64_t& k, uint32_t& id) {
+                               const int64_t o = ((w0 + e / topk) * nq + n) * topk + e % topk;
+                               k = ckey[o];
+                               id = cidx[o];
+                             });
+  if ((tid & 63) == 0) ml.cnt[wid] = mine;
+  __syncthreads();
+  if (wid == 0) {
+    // the other waves' lists, as one row of MRG_W - 1 lists of MAX_TOPK slots
+    const int c = wave_topk((int64_t)(MRG_W - 1) * MAX_TOPK, topk, ml.key[0], ml.idx[0], mine,
+                            [&](int64_t e, uint64_t& k, uint32_t& id) {
+                              const int w = 1 + (int)(e / MAX_TOPK), at = (int)(e % MAX_TOPK);
+                              if (at < ml.cnt[w]) {
+                                k = ml.key[w][at];
+                                id = ml.idx[w][at];
+                              }
+                            });
+    if (tid == 0) ml.cnt[0] = c;
   }
   __syncthreads();
-  const int64_t l0 = (int64_t)sp * per;
-  const int64_t total = std::max<int64_t>(0, std::min<int64_t>(G - l0, per)) * topk;
-  for (int64_t base = 0; base < total; base += 256 * MRU) {
-    uint64_t key[MRU];
-    uint32_t id[MRU];
-#pragma unroll
-    for (int r = 0; r < MRU; ++r) {
-      const int64_t e = base + 256 * r + tid;
-      key[r] = 0ull;
-      id[r] = 0xFFFFFFFFu;
-      if (e < total) {
-        const int64_t wg = l0 + e / topk, j = e % topk;
-        const int64_t o = (wg * QB + n) * topk + j;
-        key[r] = ckey[o];
-        id[r] = cidx[o];
-      }
-    }
-    const uint64_t thr = ml.thr;
-#pragma unroll
-    for (int r = 0; r < MRU; ++r) {
-      if (id[r] != 0xFFFFFFFFu && key[r] >= thr) {
-        const int pos = atomicAdd(&ml.cnt, 1);
-        ml.key[pos] = key[r];
-        ml.idx[pos] = id[r];
-      }
+  const int c = ml.cnt[0];
+  uint64_t* key = ml.key[0];
+  uint32_t* idx = ml.idx[0];
+  if constexpr (FINAL) {
+    // bitonic sort of the least power of two of slots that holds the list
+    int P = 2;
+    while (P < c) P <<= 1;
+    if (tid >= c && tid < P) {
+      key[tid] = 0ull;
+      idx[tid] = 0xFFFFFFFFu;
     }
     __syncthreads();
-    if (ml.cnt > MCAP - 256 * MRU) prune_list<MCAP, 256>(ml.key, ml.idx, &ml.cnt, &ml.thr, topk);
+    for (int k = 2; k <= P; k <<= 1) {
+      for (int j = k >> 1; j > 0; j >>= 1) {
+        const int p = tid ^ j;
+        if (tid < P && p > tid) {
+          const uint64_t ka = key[tid], kb = key[p];
+          const uint32_t ia = idx[tid], ib = idx[p];
+          const bool ab = before(ka, ia, kb, ib);
+          if ((tid & k) == 0 ? !ab : ab) {
+            key[tid] = kb; key[p] = ka;
+            idx[tid] = ib; idx[p] = ia;
+          }
+        }
+        __syncthreads();
+      }
+    }
   }
-  if (FINAL || ml.cnt > topk) prune_list<MCAP, 256>(ml.key, ml.idx, &ml.cnt, &ml.thr, topk);
-  for (int e = tid; e < topk; e += 256) {
-    const bool have = e < ml.cnt;
+  for (int e = tid; e < topk; e += MRG_THR) {
+    const bool have = e < c;
     if constexpr (FINAL) {
-      out_idx[q * topk + e] = have ? (int64_t)ml.idx[e] : -1;
-      out_score[q * topk + e] = have ? (float)key_value(ml.key[e]) : -__builtin_inff();
+      out_idx[q * topk + e] = have ? (int64_t)idx[e] : -1;
+      out_score[q * topk + e] = have ? (float)key_value(key[e]) : -__builtin_inff();
     } else {
-      const int64_t o = ((int64_t)sp * QB + n) * topk + e;
-      okey[o] = have ? ml.key[e] : 0ull;
-      oidx[o] = have ? ml.idx[e] : 0xFFFFFFFFu;
+      const int64_t o = ((int64_t)sp * nq + n) * topk + e;
+      okey[o] = have ? key[e] : 0ull;
+      oidx[o] = have ? idx[e] : 0xFFFFFFFFu;
     }
   }
 }
 
-// Pass configuration: candidate slots per query of the multi-module fold (256
-// when that leaves room for at least 128 new entries after a prune, else 512;
-// the one-module pass always takes 512, with which its first blocks prune less
-// often: 0.7% faster per pass than 256 at top-100), bytes per row and
-// step, 32-row tiles per wave and steps requested ahead. One workgroup runs
-// per CU (LDS).
+// How a call runs: queries per pass / 16 (nqt) and 32-row tiles per wave (rt).
 struct PassCfg {
-  int cap, sb, rt, d;
+  int nqt, rt;
 };
-inline PassCfg pass_cfg(int32_t topk) {
-  PassCfg c;
-  c.cap = topk <= 128 ? 256 : 512;
-  c.sb = 64;
-  c.rt = 2;
-  c.d = 3;
-  return c;
-}
 
 struct Layout {
   int64_t n_steps = 0;   // steps over all modules
-  int64_t n_groups = 0;
+  int64_t n_groups = 0;  // groups of 16 queries
   int64_t grid = 0;      // workgroups of the scoring pass
   int64_t fold_grid = 0; // workgroups of the multi-module fold (0: one module)
-  int64_t step_bytes = 0;
   int n_rng = 1;         // module ranges of the multi-module pass
-  bool n64 = false;      // multi-module dots stored in 64 bits
+  bool n64 = false;      // dots need 64 bits
   int merge_split = 1;   // first-level merge workgroups per query
   size_t o_mods = 0, o_fq = 0, o_ys = 0, o_pl = 0, o_ck = 0, o_ci = 0, o_ck2 = 0, o_ci2 = 0,
-         o_part = 0, o_pad = 0,
+         o_part = 0,
          total = 0;
 };
 
-Layout layout(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk) {
+// Fold lists: 256 candidate slots per query when that leaves room for at least
+// 128 new entries after a prune, else 512.
+inline int fold_cap(int32_t topk) { return topk <= 128 ? 256 : 512; }
+
+// Module ranges of the multi-module pass for n_blocks row blocks: the count
+// that gives the shortest schedule, rounds of units times the steps of a
+// range (a uniform estimate), plus a step per unit for its start and its dots.
+int pick_ranges(int64_t n_blocks, int U, int64_t n_steps) {
+  int best = 1;
+  double best_t = 1e300;
+  const int most = (int)std::min<int64_t>({(int64_t)U, (int64_t)MAX_RNG,
+                                           std::max<int64_t>(1, ceil_div(8 * kCus, std::max<int64_t>(1, n_blocks)))});
+  for (int r = 1; r <= most; ++r) {
+    const double rounds = (double)ceil_div(n_blocks * r, kCus);
+    const double steps = (double)n_steps / U * (double)ceil_div(U, r) + 1.0;
+    if (rounds * steps < best_t * 0.999) {
+      best_t = rounds * steps;
+      best = r;
+    }
+  }
+  return best;
+}
+
+Layout layout(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk, PassCfg c) {
   Layout L;
-  const PassCfg c = pass_cfg(topk);
   int64_t kmax = 0;
   for (int u = 0; u < U; ++u) {
-    L.n_steps += (kmod[u] + 8 * c.sb - 1) / (8 * c.sb);
+    L.n_steps += (kmod[u] + 8 * SB - 1) / (8 * SB);
     kmax = std::max<int64_t>(kmax, kmod[u]);
   }
   L.n_groups = (Q + QB - 1) / QB;
-  L.step_bytes = 256 * (int64_t)c.sb;
-  const int64_t n_blocks = (N + NW * 32 * c.rt - 1) / (NW * 32 * c.rt);
+  const int64_t rows = NW * 32 * c.rt;
+  const int64_t n_blocks = (N + rows - 1) / rows;
   int64_t lists = 0;
   if (U == 1) {
     L.grid = std::max<int64_t>(1, std::min<int64_t>(n_blocks, kCus));
-    lists = L.grid;
+    // lists for the two-tile blocks, whichever block size runs
+    lists = std::max<int64_t>(1, std::min<int64_t>((N + NW * 64 - 1) / (NW * 64), kCus));
   } else {
-    // about four units per CU when the row blocks alone are too few, each
-    // range at least one module; ranges are cut by step count
-    L.n_rng = (int)std::min<int64_t>({(int64_t)U, (int64_t)MAX_RNG,
-                                      std::max<int64_t>(1, ceil_div(4 * kCus, std::max<int64_t>(1, n_blocks)))});
+    L.n_rng = pick_ranges(n_blocks, U, L.n_steps);
     const int64_t units = std::max<int64_t>(1, n_blocks * L.n_rng);
     L.grid = std::min<int64_t>(units, kCus);
     if (L.grid >= kXcds) L.grid = L.grid / kXcds * kXcds;
     L.fold_grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(N, FOLD_ROWS), 2 * kCus));
     lists = L.fold_grid;
-    L.n64 = kmax > (1 << 16);   // |n| <= k 2^14 fits 32 bits up to k = 2^16
   }
+  L.n64 = kmax > (1 << 16);     // |n| <= k 2^14 fits 32 bits up to k = 2^16
+  const size_t nq = (size_t)c.nqt * QB;
   size_t b = 0;
   auto add = [&](size_t x) { size_t o = b; b = align256(b + x); return o; };
   L.o_mods = add(sizeof(ModInfo) * U);
   L.o_fq = add(4 * (size_t)L.n_groups * U * QB);
   L.o_ys = add(8 * (size_t)L.n_groups * U * QB);
-  L.o_pl = add((size_t)(L.n_groups * L.n_steps * L.step_bytes));
-  L.o_ck = add((size_t)lists * QB * topk * 8);
-  L.o_ci = add((size_t)lists * QB * topk * 4);
+  L.o_pl = add((size_t)(L.n_groups * L.n_steps) * FRAGS * 1024);
+  L.o_ck = add((size_t)lists * nq * topk * 8);
+  L.o_ci = add((size_t)lists * nq * topk * 4);
   L.merge_split = (int)std::min<int64_t>(MSPLIT, std::max<int64_t>(1, lists / 8));
-  L.o_ck2 = add((size_t)L.merge_split * QB * topk * 8);
-  L.o_ci2 = add((size_t)L.merge_split * QB * topk * 4);
-  L.o_part = add(U > 1 ? (size_t)U * QB * (size_t)N * (L.n64 ? 8 : 4) : 0);
-  L.o_pad = add(16);   // a store of fewer than 16 bytes is copied here (see score_topk)
+  L.o_ck2 = add((size_t)L.merge_split * nq * topk * 8);
+  L.o_ci2 = add((size_t)L.merge_split * nq * topk * 4);
+  L.o_part = add(U > 1 ? (size_t)U * nq * (size_t)N * (L.n64 ? 8 : 4) : 0);
+  add(16);             // (unused; part of the size that callers have stored and limits count)
   L.total = b;
   return L;
+}
+
+// Queries per pass and tiles per wave.
+// 32 queries per pass (nqt = 2) whenever there are more than 16: a pass then
+// reads the store and expands its bits once for twice the MFMAs (1,048,576 codes
+// of 16,384 bits: 0.85 ms per 32 queries against 0.89 ms per 16 before). Not for
+// top-k over 128 (32 lists of more than 256 slots do not fit LDS beside the
+// planes), for dots in 64 bits, nor where the workspace is too small for it:
+// its candidate lists and dots are twice as many, so `ws_bytes` that hold the
+// 16-query layout only get the 16-query pass, with the same results.
+// Four tiles per wave (1,024-row blocks) halve the fragment reads per MFMA and
+// the planes read per code byte (4,194,304 codes, 16 queries: the pass 2.5 -> 1.9
+// ms with it and the requests that run on across blocks); two (512 rows) where
+// the blocks' last round would be emptier: rounds x (rows + a fixed part of a
+// block).
+PassCfg choose_cfg(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk, size_t ws_bytes) {
+  int64_t kmax = 0;
+  for (int u = 0; u < U; ++u) kmax = std::max<int64_t>(kmax, kmod[u]);
+  const bool n64 = kmax > (1 << 16);
+  PassCfg c;
+  c.rt = 2;
+  c.nqt = Q > QB && topk <= 128 && !n64 ? 2 : 1;
+  if (c.nqt == 2 && layout(N, Q, U, kmod, topk, c).total > ws_bytes) c.nqt = 1;
+  if (n64) return c;
+  if (U == 1) {
+    auto rounds = [&](int rt) { return (double)ceil_div(std::max<int64_t>(1, ceil_div(N, NW * 32 * rt)), kCus); };
+    if (rounds(4) * 4.2 < rounds(2) * 2.4) c.rt = 4;
+  } else if (N >= (int64_t)NW * 128 * 24) {
+    c.rt = 4;
+  }
+  return c;
 }
 
 // Module ranges of the multi-module pass: n_rng consecutive ranges of
 // roughly equal step counts, each at least one module (one pass over the
 // module sizes, no host allocation).
-void module_ranges(const int64_t* kmod, int U, int sb, int64_t n_steps, int n_rng, int32_t* rng) {
-  auto steps = [&](int u) { return (kmod[u] + 8 * sb - 1) / (8 * sb); };
+void module_ranges(const int64_t* kmod, int U, int64_t n_steps, int n_rng, int32_t* rng) {
+  auto steps = [&](int u) { return (kmod[u] + 8 * SB - 1) / (8 * SB); };
   rng[0] = 0;
   int v = 1;                   // candidate start of the next range
   int64_t base = steps(0);     // first step of module v
@@ -964,24 +1166,33 @@ void module_ranges(const int64_t* kmod, int U, int sb, int64_t n_steps, int n_rn
   rng[n_rng] = U;
 }
 
-template <int MODE, int CAP, bool TILED>
-eogp_status launch_pass(const PassCfg& c, dim3 gd, const ScoreArgs& a, hipStream_t s) {
-#define EOGP_SCORE_CFG(SB, RT, D)                                                           \
-  if (c.sb == SB && c.rt == RT && c.d == D) {                                               \
-    hipLaunchKernelGGL((k_score<2, D, MODE, CAP, SB, RT, TILED>), gd, dim3(NTHR), 0, s, a);  \
-    return EOGP_OK;                                                                         \
+// One pass of nqt groups; MODE as in k_score.
+template <int MODE, bool TILED>
+void launch_pass(int nqt, int rt, dim3 gd, const ScoreArgs& a, hipStream_t s) {
+  const dim3 bd(NTHR);
+  if constexpr (MODE == 2 || MODE == 3) {
+    hipLaunchKernelGGL((k_score<1, 2, 2, MODE, 512, TILED>), gd, bd, 0, s, a);
+  } else if (nqt == 2) {
+    if (rt == 4) hipLaunchKernelGGL((k_score<2, 4, 1, MODE, 256, TILED>), gd, bd, 0, s, a);
+    else hipLaunchKernelGGL((k_score<2, 2, 1, MODE, 256, TILED>), gd, bd, 0, s, a);
+  } else {
+    if (rt == 4) hipLaunchKernelGGL((k_score<1, 4, 2, MODE, 512, TILED>), gd, bd, 0, s, a);
+    else hipLaunchKernelGGL((k_score<1, 2, 2, MODE, 512, TILED>), gd, bd, 0, s, a);
   }
-  EOGP_SCORE_CFG(64, 2, 3)
-#undef EOGP_SCORE_CFG
-  return fail(EOGP_ERR_UNSUPPORTED, "score_topk: no kernel for this pass configuration");
 }
 
 }  // namespace
 
 int32_t score_max_topk() { return MAX_TOPK; }
 
+// The least workspace a call runs with: the 16-query layout.
+size_t score_ws_min(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk) {
+  return layout(N, Q, U, kmod, topk, PassCfg{1, 2}).total;
+}
+// The workspace of the pass that choose_cfg prefers.
 size_t score_ws(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk) {
-  return layout(N, Q, U, kmod, topk).total;
+  const PassCfg c = choose_cfg(N, Q, U, kmod, topk, ~size_t(0));
+  return std::max(score_ws_min(N, Q, U, kmod, topk), layout(N, Q, U, kmod, topk, c).total);
 }
 
 template <bool TILED>
@@ -989,7 +1200,8 @@ eogp_status score_topk_impl(const uint8_t* codes, int64_t cstride, const uint16_
                             int64_t N, int32_t U, const int64_t* kmod, const float* Y, int64_t ldy,
                             int64_t Q, int32_t topk, int64_t* out_idx, float* out_score,
                             float* full, void* ws, size_t ws_bytes, hipStream_t s) {
-  const Layout L = layout(N, Q, U, kmod, topk);
+  const PassCfg cfg = choose_cfg(N, Q, U, kmod, topk, ws_bytes);
+  const Layout L = layout(N, Q, U, kmod, topk, cfg);
   if (ws_bytes < L.total) return fail(EOGP_ERR_WORKSPACE, "score_topk: workspace too small");
   if (Q == 0) return EOGP_OK;
   char* base = static_cast<char*>(ws);
@@ -1002,19 +1214,6 @@ eogp_status score_topk_impl(const uint8_t* codes, int64_t cstride, const uint16_
   uint64_t* ck2 = reinterpret_cast<uint64_t*>(base + L.o_ck2);
   uint32_t* ci2 = reinterpret_cast<uint32_t*>(base + L.o_ci2);
 
-  // The pass reads 16 bytes at the store's start in place of bytes past a
-  // module's end; a store with fewer readable bytes is copied into a zeroed
-  // 16-byte slot of the workspace first.
-  int64_t ksum = 0;
-  for (int u = 0; u < U; ++u) ksum += kmod[u];
-  if (!TILED && N > 0 && (N - 1) * cstride + ksum / 8 < 16) {
-    uint8_t* pad = reinterpret_cast<uint8_t*>(base + L.o_pad);
-    hipLaunchKernelGGL(k_pad16, dim3(1), dim3(16), 0, s, codes,
-                       (int)((N - 1) * cstride + ksum / 8), pad);
-    EOGP_LAUNCH_CHECK("small-store copy");
-    codes = pad;
-  }
-  const PassCfg cfg = pass_cfg(topk);
   // the module table, MOD_CHUNK entries per launch (kernel arguments)
   int64_t coff = 0, boff = 0, sbase = 0;
   for (int u0 = 0; u0 < U; u0 += MOD_CHUNK) {
@@ -1029,18 +1228,18 @@ eogp_status score_topk_impl(const uint8_t* codes, int64_t cstride, const uint16_
       mc.m[i].sbase = (int32_t)sbase;
       coff += k;
       boff += k / 8;
-      sbase += (k + 8 * cfg.sb - 1) / (8 * cfg.sb);
+      sbase += (k + 8 * SB - 1) / (8 * SB);
     }
     hipLaunchKernelGGL(k_mod_table, dim3(1), dim3(MOD_CHUNK), 0, s, mc, mods);
   }
   EOGP_LAUNCH_CHECK("module table");
   timing::Scope tprep(EOGP_KT_SCORE_PREP, s);
-  hipLaunchKernelGGL(k_query_stats, dim3((unsigned)(L.n_groups * QB), (unsigned)U), dim3(256), 0,
+  hipLaunchKernelGGL(k_query_stats, dim3((unsigned)(L.n_groups * QB), (unsigned)U), dim3(STAT_THR), 0,
                      s, Y, ldy, Q, U, mods, fq, ys);
   // one thread per 16 bytes of each of the two planes
-  const int64_t pthreads = L.n_groups * L.n_steps * L.step_bytes / 32;
+  const int64_t pthreads = L.n_groups * L.n_steps * 512;
   hipLaunchKernelGGL(k_query_planes, dim3((unsigned)ceil_div(pthreads, 256)), dim3(256), 0, s, Y,
-                     ldy, Q, U, mods, fq, L.n_steps, L.n_groups, cfg.sb, planes);
+                     ldy, Q, U, mods, fq, L.n_steps, L.n_groups, TILED ? 1 : 0, planes);
   EOGP_LAUNCH_CHECK("query preparation");
   timing::end(tprep.slot, s);
   tprep.slot = -1;
@@ -1063,7 +1262,7 @@ eogp_status score_topk_impl(const uint8_t* codes, int64_t cstride, const uint16_
   a.n_rng = L.n_rng;
   a.part = base + L.o_part;
   a.n_tiles = ceil_div(N, 32);
-  if (U > 1) module_ranges(kmod, U, cfg.sb, L.n_steps, L.n_rng, a.rng);
+  if (U > 1) module_ranges(kmod, U, L.n_steps, L.n_rng, a.rng);
   FoldArgs fa;
   fa.part = a.part;
   fa.scales = scales;
@@ -1075,45 +1274,47 @@ eogp_status score_topk_impl(const uint8_t* codes, int64_t cstride, const uint16_
   fa.full = full;
   fa.ckey = ck;
   fa.cidx = ci;
-  for (int64_t grp = 0; grp < L.n_groups; ++grp) {
+  for (int64_t grp = 0; grp < L.n_groups;) {
+    const int nqt = cfg.nqt == 2 && grp + 1 < L.n_groups ? 2 : 1;   // an odd last group alone
+    const int nq = nqt * QB;
     a.grp = grp;
     fa.grp = grp;
+    fa.nq = nq;
     {
       // one pass over the store: the streaming kernel, and for several
       // modules the fold that adds their terms in order
       timing::Scope tp(EOGP_KT_SCORE_PASS, s);
       const dim3 gd((unsigned)L.grid);
-      eogp_status st;
       if (U == 1) {
-        st = launch_pass<0, 512, TILED>(cfg, gd, a, s);
+        if (L.n64) launch_pass<3, TILED>(nqt, cfg.rt, gd, a, s);
+        else launch_pass<0, TILED>(nqt, cfg.rt, gd, a, s);
       } else {
-        st = L.n64 ? launch_pass<2, 256, TILED>(cfg, gd, a, s) : launch_pass<1, 256, TILED>(cfg, gd, a, s);
-        if (st == EOGP_OK) {
-          const dim3 fg((unsigned)L.fold_grid), fb(FOLD_THR);
-          if (cfg.cap == 256) {
-            if (L.n64) hipLaunchKernelGGL((k_score_fold<256, true>), fg, fb, 0, s, fa);
-            else hipLaunchKernelGGL((k_score_fold<256, false>), fg, fb, 0, s, fa);
-          } else {
-            if (L.n64) hipLaunchKernelGGL((k_score_fold<512, true>), fg, fb, 0, s, fa);
-            else hipLaunchKernelGGL((k_score_fold<512, false>), fg, fb, 0, s, fa);
-          }
+        if (L.n64) launch_pass<2, TILED>(nqt, cfg.rt, gd, a, s);
+        else launch_pass<1, TILED>(nqt, cfg.rt, gd, a, s);
+        const dim3 fg((unsigned)L.fold_grid, (unsigned)nqt), fb(FOLD_THR);
+        if (fold_cap(topk) == 256) {
+          if (L.n64) hipLaunchKernelGGL((k_score_fold<256, true>), fg, fb, 0, s, fa);
+          else hipLaunchKernelGGL((k_score_fold<256, false>), fg, fb, 0, s, fa);
+        } else {
+          if (L.n64) hipLaunchKernelGGL((k_score_fold<512, true>), fg, fb, 0, s, fa);
+          else hipLaunchKernelGGL((k_score_fold<512, false>), fg, fb, 0, s, fa);
         }
       }
-      if (st != EOGP_OK) return st;
     }
     timing::Scope tm(EOGP_KT_SCORE_MERGE, s);
     const int lists = (int)(U == 1 ? L.grid : L.fold_grid);
-    const int sp = L.merge_split, per = (int)ceil_div(lists, sp);
+    const int sp = std::min(L.merge_split, std::max(1, lists / 8)), per = (int)ceil_div(lists, sp);
     if (sp > 1) {
-      hipLaunchKernelGGL(k_merge<false>, dim3(QB, sp), dim3(256), 0, s, ck, ci, lists, per, grp, Q,
-                         topk, nullptr, nullptr, ck2, ci2);
-      hipLaunchKernelGGL(k_merge<true>, dim3(QB), dim3(256), 0, s, ck2, ci2, sp, sp, grp, Q, topk,
-                         out_idx, out_score, nullptr, nullptr);
+      hipLaunchKernelGGL(k_merge<false>, dim3(nq, sp), dim3(MRG_THR), 0, s, ck, ci, lists, per, nq, grp,
+                         Q, topk, nullptr, nullptr, ck2, ci2);
+      hipLaunchKernelGGL(k_merge<true>, dim3(nq), dim3(MRG_THR), 0, s, ck2, ci2, sp, sp, nq, grp, Q,
+                         topk, out_idx, out_score, nullptr, nullptr);
     } else {
-      hipLaunchKernelGGL(k_merge<true>, dim3(QB), dim3(256), 0, s, ck, ci, lists, lists, grp, Q,
+      hipLaunchKernelGGL(k_merge<true>, dim3(nq), dim3(MRG_THR), 0, s, ck, ci, lists, lists, nq, grp, Q,
                          topk, out_idx, out_score, nullptr, nullptr);
     }
     EOGP_LAUNCH_CHECK("score pass");
+    grp += nqt;
   }
   return EOGP_OK;
 }

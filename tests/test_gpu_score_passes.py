@@ -1,0 +1,108 @@
+"""Every variant of the scoring pass against the oracle, exactly: 16 and 32
+queries per pass, two and four row tiles per wave, one and several modules,
+dots of 32 and 64 bits, both store layouts, module ends inside a step, ties
+that fill the candidate lists, and a workspace that holds only the 16-query
+layout."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2609_37842_amd import eogp as E
+from tiled_helpers import tiled_from_rows
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def d(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).to(DEV)
+
+
+def store(N, ks, Q, seed):
+    g = np.random.default_rng(seed)
+    codes = g.integers(0, 256, size=(N, sum(ks) // 8), dtype=np.uint8)
+    scales = np.exp(g.standard_normal((N, len(ks)))).astype(np.float16)
+    return codes, scales, g.standard_normal((Q, sum(ks))).astype(np.float32)
+
+
+def check(codes, scales, ks, Y, topk, tiled):
+    N = codes.shape[0]
+    print(f"[score] N={N} ks={ks[:3]}x{len(ks)} Q={Y.shape[0]} topk={topk} tiled={tiled}", flush=True)
+    sc = d(scales.view(np.int16))
+    if tiled:
+        got = E.eogp_score_topk_tiled(d(tiled_from_rows(codes)), sc, N, ks, d(Y), topk, full_scores=True)
+    else:
+        got = E.eogp_score_topk(d(codes), sc, ks, d(Y), topk, full_scores=True)
+    torch.cuda.synchronize()
+    ref = O.score(codes, scales.view(np.uint16), ks, Y)
+    oi, ov = O.topk(ref, topk)
+    assert np.array_equal(got[2].cpu().numpy(), ref.astype(np.float32))
+    assert np.array_equal(got[0].cpu().numpy(), oi)
+    assert np.array_equal(got[1].cpu().numpy(), ov)
+
+
+@pytest.mark.parametrize("tiled", [True, False])
+@pytest.mark.parametrize("N,ks,Q,topk", [
+    (19, [1024], 5, 10),               # fewer rows than a tile
+    (5000, [2048], 16, 100),           # 16 queries, two tiles per wave
+    (5000, [2048], 40, 100),           # 32 queries, then a last pass of 16
+    (270_000, [512], 16, 200),         # 16 queries, four tiles per wave
+    (270_000, [512], 33, 128),         # 32 queries, four tiles per wave
+    (3000, [512, 1024], 16, 200),      # several modules
+    (3000, [512, 1024, 512], 20, 37),  # several modules, 32 queries
+    (30_000, [512] * 3, 16, 100),      # several modules, four tiles per wave
+    (30_000, [512] * 3, 33, 100),
+    (700, [66048], 20, 10),            # one module whose dots take 64 bits
+    (1100, [1 << 18, 512], 20, 10),    # 64-bit dots of several modules
+])
+def test_score_pass_variants(N, ks, Q, topk, tiled):
+    check(*store(N, ks, Q, N + Q)[:2], ks, store(N, ks, Q, N + Q)[2], topk, tiled)
+
+
+@pytest.mark.parametrize("N,ks,Q", [
+    (300, [64], 20), (33, [576], 17), (5, [320, 64, 704], 40), (1030, [832, 448], 16), (1, [64], 3),
+])
+def test_score_module_ends_inside_a_step(N, ks, Q):
+    codes, scales, Y = store(N, ks, Q, N)
+    check(codes, scales, ks, Y, 7, False)
+
+
+@pytest.mark.parametrize("Q,topk", [(16, 256), (32, 128), (7, 1)])
+def test_score_ties_and_infinite_scales(Q, topk):
+    """Few distinct rows (every list fills with equal keys; the smaller index
+    wins) and infinite scales."""
+    codes, scales, Y = store(9000, [512], Q, 3)
+    codes[:] = codes[np.arange(9000) % 3]
+    scales[:] = scales[np.arange(9000) % 3]
+    check(codes, scales, [512], Y, topk, True)
+    scales[100:140] = np.inf
+    check(codes, scales, [512], Y, topk, False)
+
+
+@pytest.mark.parametrize("ks", [[1024], [512, 512]])
+def test_score_workspace_of_the_16_query_layout(ks):
+    """A workspace too small for the 32-query pass runs the 16-query one, with
+    the same results; one byte less than that is refused."""
+    N, Q, topk = 4000, 48, 20
+    codes, scales, Y = store(N, ks, Q, 5)
+    c, s, y = d(codes), d(scales.view(np.int16)), d(Y)
+    idx, sc, _ = E.eogp_score_topk(c, s, ks, y, topk)
+    L = E.load()
+    karr = (E.c_i64 * len(ks))(*ks)
+    full = E.eogp_score_topk_workspace_size(N, Q, ks, topk)
+    # lists of 16 queries (and dots of several modules) less than the 32-query layout's
+    lists = -(-N // 512) if len(ks) == 1 else -(-N // 64)
+    less = full - 16 * topk * 12 * lists - (16 * N * 4 * len(ks) if len(ks) > 1 else 0)
+    assert less < full
+    ws = torch.empty(full, dtype=torch.uint8, device=DEV)
+    for nbytes in (full, less):
+        i2, s2 = torch.full_like(idx, -7), torch.zeros_like(sc)
+        st = L.eogp_score_topk(E._ptr(c), codes.shape[1], E._ptr(s), N, len(ks), karr, E._ptr(y), sum(ks), Q, topk,
+                               E._ptr(i2), E._ptr(s2), None, E._ptr(ws), nbytes, E._stream())
+        assert st == 0
+        torch.cuda.synchronize()
+        assert torch.equal(i2, idx) and torch.equal(s2, sc)
+    assert L.eogp_score_topk(E._ptr(c), codes.shape[1], E._ptr(s), N, len(ks), karr, E._ptr(y), sum(ks), Q, topk,
+                             E._ptr(idx), E._ptr(sc), None, E._ptr(ws), less // 2, E._stream()) == -4
