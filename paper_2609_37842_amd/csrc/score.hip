@@ -241,41 +241,66 @@ struct Cand {
 // Selection over 64 PER entries held by one wave (empty slots: key 0, index
 // 0xFFFFFFFF), of which at least topk are not empty: the entries to keep,
 // exactly topk of them, are those with key > tk, or key == tk and idx <= ti. tk
-// is found bit by bit from the top: the largest value that at least topk keys
-// reach, stopping as soon as exactly topk do (then every key >= tk is kept).
-// Only ballots and scalar counts, no barrier: about 25 rounds for scores.
+// is found bit by bit from the top, the high word before the low one: the
+// largest value that at least topk keys reach, stopping as soon as exactly topk
+// do (then every key >= tk is kept). Only ballots of 32-bit comparisons and
+// scalar counts, no barrier: about 25 rounds for scores.
 template <int PER>
 __device__ __forceinline__ void wave_select(const uint64_t (&key)[PER], const uint32_t (&idx)[PER],
                                             int topk, uint64_t& tk, uint32_t& ti) {
-  uint64_t t = 0;
-  for (int b = 63; b >= 0; --b) {
-    const uint64_t c = t | (1ull << b);
+  uint32_t hi[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) hi[j] = (uint32_t)(key[j] >> 32);
+  ti = 0xFFFFFFFFu;
+  uint32_t t = 0;
+  for (int b = 31; b >= 0; --b) {
+    const uint32_t c = t | (1u << b);
     int n = 0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) n += __popcll(__ballot(key[j] >= c));
-    if (n >= topk) {
-      t = c;
-      if (n == topk) {
-        tk = t;
-        ti = 0xFFFFFFFFu;
-        return;
-      }
+    for (int j = 0; j < PER; ++j) n += __popcll(__ballot(hi[j] >= c));
+    if (n >= topk) t = c;
+    if (n == topk) {
+      tk = (uint64_t)t << 32;
+      return;
     }
   }
-  // t is the topk-th key and more entries share it: the smallest indices win
+  // t is the high word of the topk-th key, and more than the missing entries share it
   int need = topk;
+  uint32_t lo[PER];                          // low words of the entries with that high word
+  bool in[PER];
 #pragma unroll
-  for (int j = 0; j < PER; ++j) need -= __popcll(__ballot(key[j] > t));
-  uint32_t v = 0;                            // the need-th smallest index among them
+  for (int j = 0; j < PER; ++j) {
+    need -= __popcll(__ballot(hi[j] > t));
+    in[j] = hi[j] == t;
+    lo[j] = (uint32_t)key[j];
+  }
+  uint32_t v = 0;
   for (int b = 31; b >= 0; --b) {
     const uint32_t c = v | (1u << b);
     int n = 0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) n += __popcll(__ballot(key[j] == t && idx[j] < c));
-    if (n < need) v = c;
+    for (int j = 0; j < PER; ++j) n += __popcll(__ballot(in[j] && lo[j] >= c));
+    if (n >= need) v = c;
+    if (n == need) {
+      tk = ((uint64_t)t << 32) | v;
+      return;
+    }
   }
-  tk = t;
-  ti = v;
+  tk = ((uint64_t)t << 32) | v;              // the topk-th key, shared: the smallest indices win
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    need -= __popcll(__ballot(in[j] && lo[j] > v));
+    in[j] = in[j] && lo[j] == v;
+  }
+  uint32_t w = 0;                            // the need-th smallest index among them
+  for (int b = 31; b >= 0; --b) {
+    const uint32_t c = w | (1u << b);
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) n += __popcll(__ballot(in[j] && idx[j] < c));
+    if (n < need) w = c;
+  }
+  ti = w;
 }
 
 // Writes the entries that wave_select keeps to key_o / idx_o (any order).
@@ -667,7 +692,13 @@ void k_score(ScoreArgs a) {
             const int64_t mo = (a.grp + qt) * QB + 8 * (i >> 2) + (i & 3);
             const int64_t ys = hq ? cys[mo + 4] : cys[mo];
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) nd[rt][qt][i] = (dot_t)dot(rt, qt, i, ys);
+            for (int rt = 0; rt < RT; ++rt) {
+              // (32-bit dots: the steps may wrap, the result fits)
+              if constexpr (MODE == 3) nd[rt][qt][i] = dot(rt, qt, i, ys);
+              else
+                nd[rt][qt][i] = (int32_t)(2u * (256u * (uint32_t)class_sum(rt, qt, i) +
+                                                (uint32_t)class_sum(rt, qt, i + 8)) - (uint32_t)ys);
+            }
           }
         // f(qt, i, list, exponent) for the lane's queries. The dots pass through
         // an opaque step first: each walk forms its scores anew instead of
@@ -685,9 +716,12 @@ void k_score(ScoreArgs a) {
               f(qt, i, QB * qt + i0 + 4 * hq, fx);
             }
         };
+        // s n, exact in fp64; the term is this times 2^-f
+        auto product = [&](int rt, int qt, int i) __attribute__((always_inline)) {
+          return (double)f16_bits_to_f32((uint16_t)s16[rt]) * (double)nd[rt][qt][i];
+        };
         auto score = [&](int rt, int qt, int i, int f) __attribute__((always_inline)) {
-          const double sv = (double)f16_bits_to_f32((uint16_t)s16[rt]);
-          return ldexp(sv * (double)nd[rt][qt][i], -f);
+          return ldexp(product(rt, qt, i), -f);
         };
         uint64_t pend = 0;
 #pragma unroll
@@ -736,19 +770,24 @@ void k_score(ScoreArgs a) {
               }
           });
         // a full list is pruned and the entries that did not fit are offered
-        // again (the loop condition is uniform)
+        // again (the loop condition is uniform). Most products are below the
+        // threshold times 2^f and need no more than that comparison; what is
+        // not (NaN, or a threshold not set yet, included) is compared by key.
         for (;;) {
           each_query([&](int qt, int i, int qn, int fx) __attribute__((always_inline)) {
             const uint64_t thr = cd.thr[qn];
-            const bool live = a.grp * QB + qn < a.Q;
+            const double least = ldexp(key_value(thr), fx);
+            uint32_t may = 0;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+              if (!(product(rt, qt, i) < least)) may |= 1u << rt;
+            if (a.grp * QB + qn >= a.Q) may = 0;
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
               const uint64_t bit = 1ull << (8 * NQT * rt + 8 * qt + i);
-              if (live && (pend & bit)) {
+              if ((may >> rt & 1) && (pend & bit)) {
                 const uint64_t key = order_key(score(rt, qt, i, fx));
-                if (key < thr) {
-                  pend &= ~bit;
-                } else {
+                if (key >= thr) {
                   const int pos = atomicAdd(&cd.cnt[qn], 1);
                   if (pos < CAP) {
                     cd.key[qn][pos] = key;
@@ -904,7 +943,7 @@ __global__ __launch_bounds__(FOLD_THR) void k_score_fold(FoldArgs a) {
 // workgroup per query merges those into the sorted top-k (FINAL). Each of the
 // four waves selects the top-k of its share, up to 512 entries at a time in
 // registers (wave_select), then the first wave selects among the four: no
-// barrier but one between the two. Only the final top-k is sorted. (Before, a
+// barrier but one between the two. Only the final top-k is put in order. (Before, a
 // bitonic sort of up to 1,024 entries by the whole workgroup per 512 entries,
 // one barrier per exchange stage: 49 + 46 us for the two levels at 256 lists of
 // 100 for 16 queries, now 21 + 25 us for 32.)
@@ -919,27 +958,32 @@ struct MergeList {
 // key_o / idx_o may be read by get only at the same or a later entry than
 // those already taken.
 template <typename Get>
-__device__ __forceinline__ int wave_topk(int64_t total, int topk, uint64_t* key_o, uint32_t* idx_o,
+__device__ __forceinline__ int wave_topk(int total, int topk, uint64_t* key_o, uint32_t* idx_o,
                                          int kept, Get&& get) {
   const int lane = threadIdx.x & 63;
-  for (int64_t pos = 0; pos < total; pos += 64 * MRG_PER - kept) {
+  for (int pos = 0; pos < total; pos += 64 * MRG_PER - kept) {
     // slots 0 .. kept - 1: the entries kept so far; then entries pos ..
     uint64_t key[MRG_PER];
     uint32_t id[MRG_PER];
     int have = 0;
 #pragma unroll
     for (int j = 0; j < MRG_PER; ++j) {
+      // every slot loads (a clamped entry where it has none), so that the
+      // loads of all slots are in flight together
       const int slot = 64 * j + lane;
-      key[j] = 0ull;
-      id[j] = 0xFFFFFFFFu;
+      const int e = pos + slot - kept;
+      get(e < 0 ? 0 : e < total ? e : total - 1, key[j], id[j]);
       if (slot < kept) {
         key[j] = key_o[slot];
         id[j] = idx_o[slot];
-      } else if (pos + slot - kept < total) {
-        get(pos + slot - kept, key[j], id[j]);
+      } else if (e >= total || id[j] == 0xFFFFFFFFu) {
+        key[j] = 0ull;
+        id[j] = 0xFFFFFFFFu;
       }
-      have += __popcll(__ballot(id[j] != 0xFFFFFFFFu));
     }
+#pragma unroll
+    for (int j = 0; j < MRG_PER; ++j)
+      have += __popcll(__ballot(id[j] != 0xFFFFFFFFu));
     const int before_kept = kept;
     uint64_t tk = 0;
     uint32_t ti = 0xFFFFFFFEu;               // every entry that is not empty
@@ -966,9 +1010,11 @@ __global__ __launch_bounds__(MRG_THR, 1) void k_merge(const uint64_t* __restrict
   const int l0 = sp * per, l1 = std::min(G, l0 + per);
   const int pw = (l1 - l0 + MRG_W - 1) / MRG_W;             // lists of this workgroup's waves
   const int w0 = std::min(l1, l0 + wid * pw), w1 = std::min(l1, w0 + pw);
-  const int mine = wave_topk((int64_t)(w1 - w0) * topk, topk, ml.key[wid], ml.idx[wid], 0,
-                             [&](int64_t e, uint64_t& k, uint32_t& id) {
-                               const int64_t o = ((w0 + e / topk) * nq + n) * topk + e % topk;
+  const int mine = wave_topk((w1 - w0) * topk, topk, ml.key[wid], ml.idx[wid], 0,
+                             [&](int e, uint64_t& k, uint32_t& id) {
+                               // (32-bit division: at most 512 lists of 256)
+                               const uint32_t l = (uint32_t)e / (uint32_t)topk, at = (uint32_t)e - l * topk;
+                               const int64_t o = ((int64_t)(w0 + l) * nq + n) * topk + at;
                                k = ckey[o];
                                id = cidx[o];
                              });
@@ -976,13 +1022,11 @@ __global__ __launch_bounds__(MRG_THR, 1) void k_merge(const uint64_t* __restrict
   __syncthreads();
   if (wid == 0) {
     // the other waves' lists, as one row of MRG_W - 1 lists of MAX_TOPK slots
-    const int c = wave_topk((int64_t)(MRG_W - 1) * MAX_TOPK, topk, ml.key[0], ml.idx[0], mine,
-                            [&](int64_t e, uint64_t& k, uint32_t& id) {
-                              const int w = 1 + (int)(e / MAX_TOPK), at = (int)(e % MAX_TOPK);
-                              if (at < ml.cnt[w]) {
-                                k = ml.key[w][at];
-                                id = ml.idx[w][at];
-                              }
+    const int c = wave_topk((MRG_W - 1) * MAX_TOPK, topk, ml.key[0], ml.idx[0], mine,
+                            [&](int e, uint64_t& k, uint32_t& id) {
+                              const int w = 1 + e / MAX_TOPK, at = e % MAX_TOPK;
+                              k = ml.key[w][at];
+                              id = at < ml.cnt[w] ? ml.idx[w][at] : 0xFFFFFFFFu;
                             });
     if (tid == 0) ml.cnt[0] = c;
   }
@@ -991,39 +1035,24 @@ __global__ __launch_bounds__(MRG_THR, 1) void k_merge(const uint64_t* __restrict
   uint64_t* key = ml.key[0];
   uint32_t* idx = ml.idx[0];
   if constexpr (FINAL) {
-    // bitonic sort of the least power of two of slots that holds the list
-    int P = 2;
-    while (P < c) P <<= 1;
-    if (tid >= c && tid < P) {
-      key[tid] = 0ull;
-      idx[tid] = 0xFFFFFFFFu;
+    // each entry's place is the number of entries before it
+    for (int e = tid; e < c; e += MRG_THR) {
+      const uint64_t k = key[e];
+      const uint32_t id = idx[e];
+      int at = 0;
+      for (int o = 0; o < c; ++o) at += before(key[o], idx[o], k, id) ? 1 : 0;
+      out_idx[q * topk + at] = (int64_t)id;
+      out_score[q * topk + at] = (float)key_value(k);
     }
-    __syncthreads();
-    for (int k = 2; k <= P; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        const int p = tid ^ j;
-        if (tid < P && p > tid) {
-          const uint64_t ka = key[tid], kb = key[p];
-          const uint32_t ia = idx[tid], ib = idx[p];
-          const bool ab = before(ka, ia, kb, ib);
-          if ((tid & k) == 0 ? !ab : ab) {
-            key[tid] = kb; key[p] = ka;
-            idx[tid] = ib; idx[p] = ia;
-          }
-        }
-        __syncthreads();
-      }
+    for (int e = c + tid; e < topk; e += MRG_THR) {
+      out_idx[q * topk + e] = -1;
+      out_score[q * topk + e] = -__builtin_inff();
     }
-  }
-  for (int e = tid; e < topk; e += MRG_THR) {
-    const bool have = e < c;
-    if constexpr (FINAL) {
-      out_idx[q * topk + e] = have ? (int64_t)idx[e] : -1;
-      out_score[q * topk + e] = have ? (float)key_value(key[e]) : -__builtin_inff();
-    } else {
+  } else {
+    for (int e = tid; e < topk; e += MRG_THR) {
       const int64_t o = ((int64_t)sp * nq + n) * topk + e;
-      okey[o] = have ? key[e] : 0ull;
-      oidx[o] = have ? idx[e] : 0xFFFFFFFFu;
+      okey[o] = e < c ? key[e] : 0ull;
+      oidx[o] = e < c ? idx[e] : 0xFFFFFFFFu;
     }
   }
 }
