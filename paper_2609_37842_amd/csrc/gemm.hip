@@ -1013,6 +1013,180 @@ void k_gemm_p(KParams kp) {
   }
 }
 
+// ---- few rows: the second stage of a small batch ------------------------------
+// C[M, N] = A[M, K] B[N, K]^T for M <= 32 MT (MT = 1, 2, 4) and a B that is read
+// once: bound by B's stream from HBM. k_gemm_p works on 256-row tiles, so with
+// few rows it multiplies mostly padding (64 rows, 65,536 x 32,768 fp16 P: 1,140 us
+// for 4.3 GB; here 660 us, 6.5 TB/s).
+//
+// A workgroup (8 waves) owns 256 columns and a K range, each wave 32 columns. A
+// wave streams its own B rows, 64 deep at a time (a whole 128-byte line of each
+// row, 8 lanes per row, two to four chunks ahead in registers), and turns them into
+// fragments through an LDS region of its own: no barrier on the way of the
+// stream. A is shared: its chunk is staged once per workgroup, double-buffered,
+// one barrier per chunk. K is split so that about two workgroups run per CU;
+// the partial tiles are added in split order.
+struct SkinnyParams {
+  GemmArgs g;
+  int64_t kc;       // K per split (multiple of 64)
+  int splits;
+};
+template <int AT, int AP, int BP, bool F16, int MT>
+__global__ __launch_bounds__(512) void k_gemm_skinny(SkinnyParams kp) {
+  constexpr int KC = 64, ROWS = 32 * MT;
+  constexpr int APC = ROWS * 8;              // 16-byte pieces of one A part per chunk
+  constexpr int AQ = (APC + 511) / 512;      // pieces per thread (the last round may be partial)
+  constexpr int PF = MT == 1 && BP == 1 ? 4 : 2;   // chunks of B requested ahead (a register set each)
+  const GemmArgs& g = kp.g;
+  __shared__ __attribute__((aligned(16))) uint16_t sA[2][AP][ROWS * KC];
+  __shared__ __attribute__((aligned(16))) uint16_t sB[8][BP][32 * KC];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t M = g.M, N = g.N;
+  const int64_t tiles_n = (N + 255) / 256;
+  const int64_t n0 = ((int64_t)blockIdx.x % tiles_n) * 256;
+  const int split = (int)((int64_t)blockIdx.x / tiles_n);
+  const int64_t kbeg = split * kp.kc, kend = std::min<int64_t>(g.K, kbeg + kp.kc);
+  const int64_t nc = (kend - kbeg + KC - 1) / KC;
+  // 16-byte piece c (0..7) of row r of a 128-byte-row tile (halves)
+  auto at = [](int r, int c) { return r * KC + ((c ^ (r & 7)) << 3); };
+
+  // B: instruction i loads rows 8 i + lane / 8 of the wave's 32, piece lane % 8;
+  // columns past N read the last one (never stored)
+  const int b_r = lane >> 3, b_c = lane & 7;
+  int64_t b_off[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    b_off[i] = std::min<int64_t>(n0 + 32 * wid + 8 * i + b_r, N - 1) * g.ldb;
+  // A: piece tid + 512 q is row / 8, piece % 8; rows past M read the last one
+  int64_t a_off[AQ];
+#pragma unroll
+  for (int q = 0; q < AQ; ++q) a_off[q] = std::min<int64_t>((tid + 512 * q) >> 3, M - 1) * g.lda;
+  const int a_c = tid & 7;
+
+  struct BRegs { v4u r[BP][4]; };
+  struct ARegs {
+    v4f f[AT == 0 ? AQ : 1][2];
+    v4u h[AT == 0 ? 1 : AQ];
+  };
+  // pieces beyond kend (K a multiple of 8) load the range's last piece and are zeroed
+  auto load_b = [&](int64_t ch, BRegs& R) {
+    const int64_t k = kbeg + ch * KC + 8 * b_c, kk = std::min<int64_t>(k, kend - 8);
+#pragma unroll
+    for (int p = 0; p < BP; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        // read once by this workgroup alone: a streaming load
+        R.r[p][i] = __builtin_nontemporal_load(
+            reinterpret_cast<const v4u*>((p ? g.B_lo : g.B_hi) + b_off[i] + kk));
+        if (k >= kend) R.r[p][i] = mk4(0, 0, 0, 0);
+      }
+  };
+  auto load_a = [&](int64_t ch, ARegs& R) {
+    const int64_t k = kbeg + ch * KC + 8 * a_c, kk = std::min<int64_t>(k, kend - 8);
+#pragma unroll
+    for (int q = 0; q < AQ; ++q) {
+      if constexpr (AT == 0) {
+        const float* p = static_cast<const float*>(g.A) + a_off[q] + kk;
+        R.f[q][0] = *reinterpret_cast<const v4f*>(p);
+        R.f[q][1] = *reinterpret_cast<const v4f*>(p + 4);
+        if (k >= kend) R.f[q][0] = R.f[q][1] = v4f{0.f, 0.f, 0.f, 0.f};
+      } else {
+        R.h[q] = *reinterpret_cast<const v4u*>(static_cast<const uint16_t*>(g.A) + a_off[q] + kk);
+        if (k >= kend) R.h[q] = mk4(0, 0, 0, 0);
+      }
+    }
+  };
+  auto stage_a = [&](int st, const ARegs& R) {
+#pragma unroll
+    for (int q = 0; q < AQ; ++q) {
+      const int pc = tid + 512 * q;
+      if (APC % 512 != 0 && pc >= APC) continue;
+      const int o = at(pc >> 3, a_c);
+      if constexpr (AT == 0) {
+        uint32_t h[4], l[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = R.f[q][e >> 1][2 * (e & 1)], y = R.f[q][e >> 1][2 * (e & 1) + 1];
+          h[e] = cvt_pair<F16>(x, y);
+          if constexpr (AP == 2) {
+            const f32x2v b = uncvt_pair<F16>(h[e]);
+            l[e] = cvt_pair<F16>(x - b.x, y - b.y);
+          }
+        }
+        *reinterpret_cast<v4u*>(&sA[st][0][o]) = mk4(h[0], h[1], h[2], h[3]);
+        if constexpr (AP == 2) *reinterpret_cast<v4u*>(&sA[st][AP - 1][o]) = mk4(l[0], l[1], l[2], l[3]);
+      } else {
+        *reinterpret_cast<v4u*>(&sA[st][0][o]) = R.h[q];
+      }
+    }
+  };
+
+  f32x16 acc[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+  BRegs B[PF];
+  ARegs RA;
+  auto last = [&](int64_t ch) { return std::min<int64_t>(ch, nc - 1); };
+  // prologue: A chunk 0 staged, chunk 1 requested; the first PF chunks of B requested
+  load_a(0, RA);
+#pragma unroll
+  for (int u = 0; u < PF; ++u) load_b(last(u), B[u]);
+  stage_a(0, RA);
+  load_a(last(1), RA);
+  __syncthreads();
+  auto chunk = [&](int64_t ch, int st, BRegs& R) {
+#pragma unroll
+    for (int p = 0; p < BP; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *reinterpret_cast<v4u*>(&sB[wid][p][at(8 * i + b_r, b_c)]) = R.r[p][i];
+    if (ch + PF < nc) load_b(ch + PF, R);
+#pragma unroll
+    for (int j = 0; j < KC / 16; ++j) {
+      const int c = 2 * j + (lane >> 5);
+      v4u fb[BP], fa[AP][MT];
+#pragma unroll
+      for (int p = 0; p < BP; ++p) fb[p] = *reinterpret_cast<const v4u*>(&sB[wid][p][at(lane & 31, c)]);
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int p = 0; p < AP; ++p)
+          fa[p][i] = *reinterpret_cast<const v4u*>(&sA[st][p][at(32 * i + (lane & 31), c)]);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) acc[i] = mfma32<F16>(fa[0][i], fb[0], acc[i]);
+      if constexpr (BP == 2)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[i] = mfma32<F16>(fa[0][i], fb[BP - 1], acc[i]);
+      if constexpr (AP == 2)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[i] = mfma32<F16>(fa[AP - 1][i], fb[0], acc[i]);
+    }
+    stage_a(st ^ 1, RA);               // chunk ch + 1 (past the end: a copy, unused)
+    load_a(last(ch + 2), RA);
+    __syncthreads();
+  };
+  for (int64_t ch = 0; ch < nc; ch += PF)
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+      if (ch + u < nc) chunk(ch + u, u & 1, B[u]);
+  float* C = g.C;
+  int64_t ldc = g.ldc;
+  if (kp.splits > 1) {
+    C = g.partial + (int64_t)split * M * N;
+    ldc = N;
+  }
+  const int64_t col = n0 + 32 * wid + (lane & 31);
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t row = 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+      if (row < M && col < N) C[row * ldc + col] = acc[i][r];
+    }
+}
+
 // C[row, col] = sum over splits, in split order, of the partial tiles. Four
 // consecutive columns per thread (16-byte loads) when N and ldc allow it.
 __global__ void k_split_sum(const float* __restrict__ part, int splits, int64_t M, int64_t N,
@@ -1056,9 +1230,42 @@ void pick(const KParams& kp, bool av, bool bc, unsigned grid, hipStream_t s) {
   }
 }
 
+// k_gemm_skinny applies: at most 128 known rows, fp32 output in place, 16-byte
+// aligned operand rows and K a multiple of 8. Above 128 rows the tiles of
+// k_gemm_p are at least half full and the time is no longer B's stream alone.
+constexpr int64_t kSkinnyRows = 128;
+inline bool skinny(const GemmArgs& g, bool av) {
+  return av && g.M <= kSkinnyRows && !g.M_dev && !g.a_rows && !g.CT && g.a_scale == 1.f && g.K % 8 == 0 &&
+         g.ldb % 8 == 0 && (uintptr_t)g.B_hi % 16 == 0 && (!g.B_lo || (uintptr_t)g.B_lo % 16 == 0);
+}
+template <int AT, int AP, int BP, bool F16>
+eogp_status launch_skinny(const GemmArgs& g, hipStream_t s) {
+  SkinnyParams kp;
+  kp.g = g;
+  kp.splits = 1;
+  const int64_t chunks = ceil_div(g.K, (int64_t)64), tiles = ceil_div(g.N, (int64_t)256);
+  if (g.partial)   // about two workgroups per CU, at least 8 chunks each
+    kp.splits = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)g.max_splits, ceil_div(2 * kCus, tiles), chunks / 8}));
+  kp.kc = ceil_div(chunks, (int64_t)kp.splits) * 64;
+  kp.splits = (int)ceil_div(g.K, kp.kc);
+  timing::Scope ts(g.timing_class, s);
+  const dim3 gd((unsigned)(tiles * kp.splits)), bd(512);
+  if (g.M <= 32) hipLaunchKernelGGL((k_gemm_skinny<AT, AP, BP, F16, 1>), gd, bd, 0, s, kp);
+  else if (g.M <= 64) hipLaunchKernelGGL((k_gemm_skinny<AT, AP, BP, F16, 2>), gd, bd, 0, s, kp);
+  else hipLaunchKernelGGL((k_gemm_skinny<AT, AP, BP, F16, 4>), gd, bd, 0, s, kp);
+  EOGP_LAUNCH_CHECK("gemm launch (few rows)");
+  if (kp.splits > 1) {
+    split_sum(g, kp.splits, s);
+    EOGP_LAUNCH_CHECK("gemm split sum");
+  }
+  return EOGP_OK;
+}
+
 template <int AT, int AP, int BP, bool F16>
 eogp_status launch(const GemmArgs& g, bool av, bool bc, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return EOGP_OK;
+  if constexpr (AT != 2)
+    if (skinny(g, av)) return launch_skinny<AT, AP, BP, F16>(g, s);
   const int64_t pad256 = ((g.N + 255) / 256) * 256, pad128 = ((g.N + 127) / 128) * 128;
   const bool wide = pad256 * 10 <= pad128 * 11;      // at most 10% more padding
   const int bn = wide ? 256 : 128;
