@@ -136,9 +136,8 @@ eogp_status eogp_plan_set_input_exponents(eogp_plan* plan, int32_t e_acts, int32
  *
  *   acts       [N, T, d_in]  in `in_dtype` (EOGP_F32 or EOGP_BF16); token
  *              (i, t) starts at element (i*T + t) * ld_acts (ld_acts >= d_in,
- *              or 0 for d_in). Rows whose byte offset is a multiple of 16 take
- *              the fast load path (fp32: ld_acts % 4 == 0; bf16: % 8 == 0);
- *              16-bit rows must satisfy it.
+ *              or 0 for d_in). fp32 rows may start at any element; bf16 rows
+ *              must start on 16-byte boundaries (ld_acts % 8 == 0).
  *   out_grads  [N, T, d_out] in `in_dtype`, token stride ld_grads likewise.
  *   token_mask [N, T] uint8, or NULL for all tokens valid. Masked tokens are
  *              never read and may hold anything, NaN included.

@@ -167,8 +167,6 @@ eogp_status pca_project(const void* Z, eogp_dtype z_dtype, int64_t ldz, int64_t 
   }
   g.B_hi = static_cast<const uint16_t*>(P);
   g.ldb = ldp;
-  // A caller's P needs no bounds checks when its shape already matches the tiles.
-  g.b_padded = (m % 32 == 0) && (k % 256 == 0);
   // 16-bit Z has P's type (checked by the caller): one product on that type's MFMA
   if (z_dtype != EOGP_F32) return gemm_nt(g, AType::B16, 1, 1, p_dtype == EOGP_F16, s);
   return gemm_nt(g, AType::F32, accurate ? 2 : 1, 1, p_dtype == EOGP_F16, s);

@@ -24,8 +24,8 @@ struct GemmArgs {
   const uint16_t* B_hi = nullptr;
   const uint16_t* B_lo = nullptr;
   int64_t ldb = 0;
-  // B is a padded panel: at least round_up(N, 256) rows and round_up(K, 32)
-  // columns per row are readable, zero beyond N and K.
+  // B is a padded panel: round_up(K, 32) columns per row are readable, zero
+  // beyond K (else a ragged last K-slice of B is loaded with bounds checks).
   bool b_padded = false;
   float* C = nullptr;
   int64_t ldc = 0;

@@ -17,8 +17,8 @@
 // padding of the last column tile stages its share and skips its fragment
 // reads and MFMAs.
 //
-// k_gemm (everything else: bf16x3 products, unaligned or bounds-checked
-// operands). A 512-thread workgroup (8 waves, two per SIMD)
+// k_gemm (everything else: bf16x3 products, B rows off 16-byte boundaries,
+// which are loaded element by element). A 512-thread workgroup (8 waves, two per SIMD)
 // owns a 256 x BN tile (BN = 256 or 128, whichever pads N less); each wave
 // computes 128 x BN/4. Slice k+1 sits in registers while slice k is multiplied
 // from LDS; then it is converted and written to the other stage and slice k+2
@@ -30,9 +30,10 @@
 // (whole rows, 4 or 8 lanes per row) free of bank conflicts. Rows beyond M
 // read a copy of a valid row (their products land in output rows that are
 // never stored, or in fp16 output rows nobody reads), and a ragged last
-// K-slice is processed first, by the only bounds-checked load. B operands are
-// padded panels (rows to 256, K to a multiple of 32, zero-filled) or, for
-// general caller layouts, checked loads.
+// K-slice is processed first, by the only bounds-checked load. fp32 A rows may
+// start at any element: 16-byte loads need no more than element alignment (128
+// examples of an unpadded 769 -> 768 module in the accurate mode, whose A rows
+// were loaded element by element before: 423 -> 394 us).
 //
 // Precision. fp32 A is converted while it is staged: rounded to the MFMA type,
 // or split into high and low parts (accurate mode), whose cross terms
@@ -76,6 +77,10 @@ __global__ void k_zero_sched(int32_t* __restrict__ c) {
 
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+// Four fp32 values at any 4-byte boundary: one 16-byte load (gfx950 loads need
+// no more than element alignment). Rows as a model leaves them, such as 769
+// fp32 wide, so take the same path as padded ones.
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ v4u mk4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
   v4u r;
@@ -209,9 +214,9 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, float* C, int64_t 
     }
 }
 
-// AT: 0 = fp32 A, 1 = 16-bit A. AV: A rows allow 16-byte loads (else fp32 A is
-// loaded one element per lane, 32 lanes per row). BC: B is bounds-checked.
-template <int AT, int AP, int BP, bool F16, int BN, bool AV, bool BC>
+// AT: 0 = fp32 A, 1 = 16-bit A. BC: B rows are not on 16-byte boundaries (loaded
+// element by element).
+template <int AT, int AP, int BP, bool F16, int BN, bool BC>
 __global__ __launch_bounds__(NTHR, 1) void k_gemm(KParams kp) {
   constexpr int WI = 4;                  // 32-high row blocks per wave (128 rows)
   constexpr int WJ = BN / 128;           // 32-wide column blocks per wave (BN/4 columns)
@@ -249,12 +254,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_gemm(KParams kp) {
   //   B:        4 lanes per row per part,    rows (tid >> 2) + 64 q, q < BN/64.
   constexpr int AQ = AT == 0 ? 4 : 2;     // A pieces per thread per slice
   constexpr int BQ = BN / 128;            // B pieces per thread per slice and part
-  constexpr int NE = BM / (NTHR / 32);    // element A path: rows per thread
   const int a_r0 = AT == 0 ? (tid >> 3) : (tid >> 2);
   const int a_rs = AT == 0 ? NTHR / 8 : NTHR / 4;
   const int a_pc = AT == 0 ? (tid & 7) : (tid & 3);   // piece index within the row
   const int b_r0 = tid >> 2, b_pc = tid & 3;
-  const int sc = tid & 31, sr = tid >> 5;   // element A path: column, first row (rows sr + 16e)
 
   for (int64_t u = t_begin; u < t_end; u += t_step) {
     int64_t t;
@@ -283,12 +286,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_gemm(KParams kp) {
       sOff[tid] = src * g.lda;
     }
     __syncthreads();
-    constexpr bool A16B = (AT == 1) || AV;      // 16-byte A path
-    int64_t a_off[A16B ? AQ : 1];
-    if constexpr (A16B) {
+    int64_t a_off[AQ];
 #pragma unroll
-      for (int q = 0; q < AQ; ++q) a_off[q] = sOff[a_r0 + a_rs * q];
-    }
+    for (int q = 0; q < AQ; ++q) a_off[q] = sOff[a_r0 + a_rs * q];
     // B rows n0 + b_r0 + 64 q; rows beyond N (which feed unstored columns)
     // read row 0 instead.
     int64_t b_off[BQ];
@@ -305,11 +305,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_gemm(KParams kp) {
     };
 
     // Register staging of one slice: A rows (from HBM) and B panel rows (small,
-    // L2-resident). On the 16-byte paths A is kept in two buffers, so each A
-    // slice is requested two slices before it is staged; B one slice before.
+    // L2-resident). A is kept in two buffers, so each A slice is requested two
+    // slices before it is staged; B one slice before.
     struct ARegs {
-      v4f ra[AT == 0 && AV ? AQ : 1];       // fp32 A (16-byte path)
-      float re[AT == 0 && !AV ? NE : 1];    // fp32 A (element path)
+      v4f ra[AT == 0 ? AQ : 1];             // fp32 A
       v4u ra16[AT == 0 ? 1 : AQ];           // 16-bit A
     };
     struct BRegs {
@@ -322,13 +321,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_gemm(KParams kp) {
     auto load_a = [&](int64_t k0, ARegs& R) {
       if constexpr (AT == 0) {
         const float* A = static_cast<const float*>(g.A);
-        if constexpr (AV) {
 #pragma unroll
-          for (int q = 0; q < AQ; ++q) R.ra[q] = *reinterpret_cast<const v4f*>(A + a_off[q] + k0 + 4 * a_pc);
-        } else {
-#pragma unroll
-          for (int e = 0; e < NE; ++e) R.re[e] = A[sOff[sr + (NTHR / 32) * e] + k0 + sc];
-        }
+        for (int q = 0; q < AQ; ++q) R.ra[q] = *reinterpret_cast<const v4fu*>(A + a_off[q] + k0 + 4 * a_pc);
       } else {
         const uint16_t* A = static_cast<const uint16_t*>(g.A);
 #pragma unroll
@@ -359,21 +353,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_gemm(KParams kp) {
     auto load_tail = [&](int64_t k0, ARegs& RA, BRegs& R) {
       if constexpr (AT == 0) {
         const float* A = static_cast<const float*>(g.A);
-        if constexpr (AV) {
 #pragma unroll
-          for (int q = 0; q < AQ; ++q) {
-            const int64_t kk = k0 + 4 * a_pc;
-            v4f x;
-            x.x = (kk + 0 < kend) ? A[a_off[q] + kk + 0] : 0.f;
-            x.y = (kk + 1 < kend) ? A[a_off[q] + kk + 1] : 0.f;
-            x.z = (kk + 2 < kend) ? A[a_off[q] + kk + 2] : 0.f;
-            x.w = (kk + 3 < kend) ? A[a_off[q] + kk + 3] : 0.f;
-            RA.ra[q] = x;
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < NE; ++e)
-            RA.re[e] = (k0 + sc < kend) ? A[sOff[sr + (NTHR / 32) * e] + k0 + sc] : 0.f;
+        for (int q = 0; q < AQ; ++q) {
+          const int64_t kk = k0 + 4 * a_pc;
+          v4f x;
+          x.x = (kk + 0 < kend) ? A[a_off[q] + kk + 0] : 0.f;
+          x.y = (kk + 1 < kend) ? A[a_off[q] + kk + 1] : 0.f;
+          x.z = (kk + 2 < kend) ? A[a_off[q] + kk + 2] : 0.f;
+          x.w = (kk + 3 < kend) ? A[a_off[q] + kk + 3] : 0.f;
+          RA.ra[q] = x;
         }
       } else {
         const uint16_t* A = static_cast<const uint16_t*>(g.A);
@@ -409,40 +397,27 @@ __global__ __launch_bounds__(NTHR, 1) void k_gemm(KParams kp) {
     // they are.
     auto stage = [&](int st, const ARegs& RA, const BRegs& R) {
       const v4f* ra = RA.ra;
-      const float* re = RA.re;
       const v4u* ra16 = RA.ra16;
       const auto& rb = R.rb;
       if constexpr (AT == 0) {
-        if constexpr (AV) {
-          // 4 floats = half of a 16-byte chunk of 8 halves
+        // 4 floats = half of a 16-byte chunk of 8 halves
 #pragma unroll
-          for (int q = 0; q < AQ; ++q) {
-            const int r = a_r0 + a_rs * q;
-            const int o = swz(r, a_pc >> 1) + 4 * (a_pc & 1);
-            v4f x = ra[q];
-            if constexpr (F16) x *= a_scale;
-            const uint32_t h0 = cvt_pair<F16>(x.x, x.y), h1 = cvt_pair<F16>(x.z, x.w);
-            v2u hv;
-            hv.x = h0;
-            hv.y = h1;
-            *reinterpret_cast<v2u*>(&sA[st][0][o]) = hv;
-            if constexpr (AP == 2) {
-              const f32x2v b0 = uncvt_pair<F16>(h0), b1 = uncvt_pair<F16>(h1);
-              v2u lv;
-              lv.x = cvt_pair<F16>(x.x - b0.x, x.y - b0.y);
-              lv.y = cvt_pair<F16>(x.z - b1.x, x.w - b1.y);
-              *reinterpret_cast<v2u*>(&sA[st][AP - 1][o]) = lv;
-            }
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < NE; ++e) {
-            const int r = sr + (NTHR / 32) * e;
-            const int o = swz(r, sc >> 3) + (sc & 7);
-            const float x = F16 ? re[e] * a_scale : re[e];
-            const uint16_t h = cvt16<F16>(x);
-            sA[st][0][o] = h;
-            if constexpr (AP == 2) sA[st][AP - 1][o] = cvt16<F16>(x - back16<F16>(h));
+        for (int q = 0; q < AQ; ++q) {
+          const int r = a_r0 + a_rs * q;
+          const int o = swz(r, a_pc >> 1) + 4 * (a_pc & 1);
+          v4f x = ra[q];
+          if constexpr (F16) x *= a_scale;
+          const uint32_t h0 = cvt_pair<F16>(x.x, x.y), h1 = cvt_pair<F16>(x.z, x.w);
+          v2u hv;
+          hv.x = h0;
+          hv.y = h1;
+          *reinterpret_cast<v2u*>(&sA[st][0][o]) = hv;
+          if constexpr (AP == 2) {
+            const f32x2v b0 = uncvt_pair<F16>(h0), b1 = uncvt_pair<F16>(h1);
+            v2u lv;
+            lv.x = cvt_pair<F16>(x.x - b0.x, x.y - b0.y);
+            lv.y = cvt_pair<F16>(x.z - b1.x, x.w - b1.y);
+            *reinterpret_cast<v2u*>(&sA[st][AP - 1][o]) = lv;
           }
         }
       } else {
@@ -509,52 +484,34 @@ __global__ __launch_bounds__(NTHR, 1) void k_gemm(KParams kp) {
       load_b(slice_k0(0), RB);
     }
     stage(0, A0, RB);
-    if constexpr (AV || AT == 1) {
-      // slice 1 into A1 and RB, slice 2 requested into A0 (with a single
-      // slice there is nothing to request: clamp would name the ragged slice)
-      if (nk > 1) {
-        load_a(clamp(1), A1);
-        load_b(clamp(1), RB);
-        load_a(clamp(2), A0);
-      }
-      __syncthreads();
-      // Steady state, two slices per trip, branch-free: on entry slice p is in
-      // LDS stage 0, slice p+1 in A1 and RB, slice p+2 in flight into A0.
-      int64_t p = 0;
-      for (; p + 2 < nk; p += 2) {
-        compute(0);
-        stage(1, A1, RB);                               // slice p+1
-        load_a(clamp(p + 3), A1);
-        load_b(clamp(p + 2), RB);
-        __syncthreads();
-        compute(1);
-        stage(0, A0, RB);                               // slice p+2
-        load_a(clamp(p + 4), A0);
-        load_b(clamp(p + 3), RB);
-        __syncthreads();
-      }
+    // slice 1 into A1 and RB, slice 2 requested into A0 (with a single
+    // slice there is nothing to request: clamp would name the ragged slice)
+    if (nk > 1) {
+      load_a(clamp(1), A1);
+      load_b(clamp(1), RB);
+      load_a(clamp(2), A0);
+    }
+    __syncthreads();
+    // Steady state, two slices per trip, branch-free: on entry slice p is in
+    // LDS stage 0, slice p+1 in A1 and RB, slice p+2 in flight into A0.
+    int64_t p = 0;
+    for (; p + 2 < nk; p += 2) {
       compute(0);
-      if (p + 1 < nk) {
-        stage(1, A1, RB);
-        __syncthreads();
-        compute(1);
-      }
-    } else {
-      // element path: one register slice, requested one slice ahead
-      if (nk > 1) {
-        load_a(clamp(1), A0);
-        load_b(clamp(1), RB);
-      }
+      stage(1, A1, RB);                               // slice p+1
+      load_a(clamp(p + 3), A1);
+      load_b(clamp(p + 2), RB);
       __syncthreads();
-      for (int64_t kt = 0; kt + 1 < nk; ++kt) {
-        const int st = (int)(kt & 1);
-        compute(st);
-        stage(st ^ 1, A0, RB);                          // slice kt+1
-        load_a(clamp(kt + 2), A0);
-        load_b(clamp(kt + 2), RB);
-        __syncthreads();
-      }
-      compute((int)((nk - 1) & 1));
+      compute(1);
+      stage(0, A0, RB);                               // slice p+2
+      load_a(clamp(p + 4), A0);
+      load_b(clamp(p + 3), RB);
+      __syncthreads();
+    }
+    compute(0);
+    if (p + 1 < nk) {
+      stage(1, A1, RB);
+      __syncthreads();
+      compute(1);
     }
 
     // epilogue: lane holds column (lane & 31), rows 8*(r/4) + 4*(lane/32) + r%4
@@ -579,8 +536,8 @@ inline bool use_buffer_b(const GemmArgs& g) {
 }
 
 // AT: 0 = fp32 A, 1 = 16-bit A used as it is, 2 = bf16 A widened, scaled
-// and rounded to fp16 while it is staged (all with 16-byte aligned rows); B is
-// a padded panel; one part each; no split-K.
+// and rounded to fp16 while it is staged (16-bit rows on 16-byte boundaries);
+// one part each; B rows on 16-byte boundaries.
 // BB: B through a range-checked buffer descriptor (padding rows skipped);
 // else plain loads with padding rows mapped to row 0.
 // NWV: waves per workgroup (4 or 8), NWV / 4 per SIMD.
@@ -732,7 +689,7 @@ void k_gemm_p(KParams kp) {
     auto load_a = [&](int64_t k0, ARegs& R) {
       if constexpr (AT == 0) {
 #pragma unroll
-        for (int q = 0; q < AQ; ++q) R.ra[q] = *reinterpret_cast<const v4f*>(pa32[q] + k0);
+        for (int q = 0; q < AQ; ++q) R.ra[q] = *reinterpret_cast<const v4fu*>(pa32[q] + k0);
       } else {
 #pragma unroll
         for (int q = 0; q < AQ; ++q) R.ra16[q] = *reinterpret_cast<const v4u*>(pa16[q] + k0);
@@ -748,8 +705,8 @@ void k_gemm_p(KParams kp) {
           R.rb[q] = *(const __attribute__((address_space(1))) v4u*)(pb[q] + k0);
       }
     };
-    // The ragged slice: element-wise, bounds-checked (B is a padded panel, so
-    // its columns up to round_up(K, 32) are readable and zero beyond K).
+    // The ragged slice: element-wise, bounds-checked (a padded B panel's columns
+    // up to round_up(K, 32) are readable and zero beyond K).
     auto load_tail = [&](int64_t k0, ARegs& RA, BRegs& R) {
       if constexpr (AT == 0) {
         const float* A = static_cast<const float*>(g.A);
@@ -776,7 +733,17 @@ void k_gemm_p(KParams kp) {
           RA.ra16[q] = mk4(pack2(h[0], h[1]), pack2(h[2], h[3]), pack2(h[4], h[5]), pack2(h[6], h[7]));
         }
       }
-      load_b(k0, R);
+      if (AT == 2 || g.b_padded) {           // (AT 2 is a rotation's: its B is a panel)
+        load_b(k0, R);
+      } else {
+#pragma unroll
+        for (int q = 0; q < BQ; ++q) {
+          uint32_t h[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) h[e] = k0 + 8 * b_pc + e < kend ? (uint32_t)pb[q][k0 + e] : 0u;
+          R.rb[q] = mk4(pack2(h[0], h[1]), pack2(h[2], h[3]), pack2(h[4], h[5]), pack2(h[6], h[7]));
+        }
+      }
     };
     auto stage_a = [&](int st, const ARegs& RA, int q0, int q1) {
       if constexpr (AT == 0) {
@@ -1088,8 +1055,8 @@ __global__ __launch_bounds__(512) void k_gemm_skinny(SkinnyParams kp) {
     for (int q = 0; q < AQ; ++q) {
       if constexpr (AT == 0) {
         const float* p = static_cast<const float*>(g.A) + a_off[q] + kk;
-        R.f[q][0] = *reinterpret_cast<const v4f*>(p);
-        R.f[q][1] = *reinterpret_cast<const v4f*>(p + 4);
+        R.f[q][0] = *reinterpret_cast<const v4fu*>(p);
+        R.f[q][1] = *reinterpret_cast<const v4fu*>(p + 4);
         if (k >= kend) R.f[q][0] = R.f[q][1] = v4f{0.f, 0.f, 0.f, 0.f};
       } else {
         R.h[q] = *reinterpret_cast<const v4u*>(static_cast<const uint16_t*>(g.A) + a_off[q] + kk);
@@ -1218,25 +1185,17 @@ void split_sum(const GemmArgs& g, int splits, hipStream_t s) {
 }
 
 template <int AT, int AP, int BP, bool F16, int BN>
-void pick(const KParams& kp, bool av, bool bc, unsigned grid, hipStream_t s) {
-  if constexpr (AT == 0) {
-    if (av && !bc) hipLaunchKernelGGL((k_gemm<AT, AP, BP, F16, BN, true, false>), dim3(grid), dim3(NTHR), 0, s, kp);
-    else if (av && bc) hipLaunchKernelGGL((k_gemm<AT, AP, BP, F16, BN, true, true>), dim3(grid), dim3(NTHR), 0, s, kp);
-    else if (!bc) hipLaunchKernelGGL((k_gemm<AT, AP, BP, F16, BN, false, false>), dim3(grid), dim3(NTHR), 0, s, kp);
-    else hipLaunchKernelGGL((k_gemm<AT, AP, BP, F16, BN, false, true>), dim3(grid), dim3(NTHR), 0, s, kp);
-  } else {
-    if (!bc) hipLaunchKernelGGL((k_gemm<AT, AP, BP, F16, BN, true, false>), dim3(grid), dim3(NTHR), 0, s, kp);
-    else hipLaunchKernelGGL((k_gemm<AT, AP, BP, F16, BN, true, true>), dim3(grid), dim3(NTHR), 0, s, kp);
-  }
+void pick(const KParams& kp, bool b16, unsigned grid, hipStream_t s) {
+  if (b16) hipLaunchKernelGGL((k_gemm<AT, AP, BP, F16, BN, false>), dim3(grid), dim3(NTHR), 0, s, kp);
+  else hipLaunchKernelGGL((k_gemm<AT, AP, BP, F16, BN, true>), dim3(grid), dim3(NTHR), 0, s, kp);
 }
 
-// k_gemm_skinny applies: at most 128 known rows, fp32 output in place, 16-byte
-// aligned operand rows and K a multiple of 8. Above 128 rows the tiles of
+// k_gemm_skinny applies: at most 128 known rows, fp32 output in place, 16-bit
+// operand rows on 16-byte boundaries and K a multiple of 8. Above 128 rows the tiles of
 // k_gemm_p are at least half full and the time is no longer B's stream alone.
 constexpr int64_t kSkinnyRows = 128;
-inline bool skinny(const GemmArgs& g, bool av) {
-  return av && g.M <= kSkinnyRows && !g.M_dev && !g.a_rows && !g.CT && g.a_scale == 1.f && g.K % 8 == 0 &&
-         g.ldb % 8 == 0 && (uintptr_t)g.B_hi % 16 == 0 && (!g.B_lo || (uintptr_t)g.B_lo % 16 == 0);
+inline bool skinny(const GemmArgs& g, bool b16) {
+  return b16 && g.M <= kSkinnyRows && !g.M_dev && !g.a_rows && !g.CT && g.a_scale == 1.f && g.K % 8 == 0;
 }
 template <int AT, int AP, int BP, bool F16>
 eogp_status launch_skinny(const GemmArgs& g, hipStream_t s) {
@@ -1262,10 +1221,10 @@ eogp_status launch_skinny(const GemmArgs& g, hipStream_t s) {
 }
 
 template <int AT, int AP, int BP, bool F16>
-eogp_status launch(const GemmArgs& g, bool av, bool bc, hipStream_t s) {
+eogp_status launch(const GemmArgs& g, bool b16, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return EOGP_OK;
   if constexpr (AT != 2)
-    if (skinny(g, av)) return launch_skinny<AT, AP, BP, F16>(g, s);
+    if (skinny(g, b16)) return launch_skinny<AT, AP, BP, F16>(g, s);
   const int64_t pad256 = ((g.N + 255) / 256) * 256, pad128 = ((g.N + 127) / 128) * 128;
   const bool wide = pad256 * 10 <= pad128 * 11;      // at most 10% more padding
   const int bn = wide ? 256 : 128;
@@ -1285,7 +1244,7 @@ eogp_status launch(const GemmArgs& g, bool av, bool bc, hipStream_t s) {
     }
   }
   if constexpr (AP == 1 && BP == 1) {
-    if (av && !bc) {
+    if (b16) {
       // single-pass product: the pipelined kernel (kPipeWaves waves), 256 x 256 tiles.
       // Split K (host-known M, scratch given) when that shortens the
       // estimated time: rounds of units x slices per unit, plus the partial
@@ -1336,8 +1295,8 @@ eogp_status launch(const GemmArgs& g, bool av, bool bc, hipStream_t s) {
   int64_t grid = std::min<int64_t>(tiles * kp.splits, kCus);
   if (grid >= kXcds) grid = grid / kXcds * kXcds;
   timing::Scope ts(g.timing_class, s);
-  if (wide) pick<AT, AP, BP, F16, 256>(kp, av, bc, (unsigned)grid, s);
-  else pick<AT, AP, BP, F16, 128>(kp, av, bc, (unsigned)grid, s);
+  if (wide) pick<AT, AP, BP, F16, 256>(kp, b16, (unsigned)grid, s);
+  else pick<AT, AP, BP, F16, 128>(kp, b16, (unsigned)grid, s);
   EOGP_LAUNCH_CHECK("gemm launch");
   if (kp.splits > 1) {
     split_sum(g, kp.splits, s);
@@ -1354,14 +1313,17 @@ size_t gemm_partial_bytes(int64_t M, int64_t N, int max_splits) {
 }
 
 namespace {
-// The pipelined kernel applies: single-pass product, 16-byte aligned A rows,
-// B a padded panel on 16-byte boundaries.
+// Every B row starts on a 16-byte boundary.
+bool b_rows16(const GemmArgs& g) {
+  return g.ldb % 8 == 0 && (uintptr_t)g.B_hi % 16 == 0 && (g.B_lo == nullptr || (uintptr_t)g.B_lo % 16 == 0);
+}
+// So does every A row, where it must: fp32 rows may start anywhere.
+bool a_rows_ok(const GemmArgs& g, AType a_type) {
+  return a_type == AType::F32 || (g.lda % 8 == 0 && (uintptr_t)g.A % 16 == 0);
+}
+// The pipelined kernel applies (to a single-pass product).
 bool pipelined(const GemmArgs& g, AType a_type) {
-  const int a_align = a_type == AType::F32 ? 4 : 8;
-  const bool av = (g.lda % a_align == 0) && ((uintptr_t)g.A % 16 == 0);
-  const bool bc = !(g.b_padded && (g.ldb % 8 == 0) && ((uintptr_t)g.B_hi % 16 == 0) &&
-                    (g.B_lo == nullptr || (uintptr_t)g.B_lo % 16 == 0));
-  return av && !bc && !g.partial;
+  return a_rows_ok(g, a_type) && b_rows16(g) && !g.partial;
 }
 }  // namespace
 
@@ -1413,27 +1375,23 @@ eogp_status gemm_nt2(const GemmArgs& g1, const GemmArgs& g2, AType a_type, int a
 eogp_status gemm_nt(const GemmArgs& g, AType a_type, int a_parts, int b_parts, bool f16,
                     hipStream_t s) {
   const bool A32 = a_type == AType::F32;
-  const int a_align = A32 ? 4 : 8;
-  const bool av = (g.lda % a_align == 0) && ((uintptr_t)g.A % 16 == 0);
-  if (!A32 && !av) return fail(EOGP_ERR_UNSUPPORTED, "gemm: 16-bit A rows must be 16-byte aligned");
-  // B needs no checks when rows are padded to the tile and K to the slice.
-  const bool bc = !(g.b_padded && (g.ldb % 8 == 0) && ((uintptr_t)g.B_hi % 16 == 0) &&
-                    (g.B_lo == nullptr || (uintptr_t)g.B_lo % 16 == 0));
+  if (!a_rows_ok(g, a_type)) return fail(EOGP_ERR_UNSUPPORTED, "gemm: 16-bit A rows must be 16-byte aligned");
+  const bool b16 = b_rows16(g);
   if (b_parts == 2 && g.B_lo == nullptr) return fail(EOGP_ERR_INVALID, "gemm: missing B low part");
   if (a_type == AType::BF16_AS_F16) {
     if (a_parts != 1 || b_parts != 1 || !f16)
       return fail(EOGP_ERR_UNSUPPORTED, "gemm: bf16 A widened to fp16 is a single fp16 product");
-    return launch<2, 1, 1, true>(g, av, bc, s);
+    return launch<2, 1, 1, true>(g, b16, s);
   }
   if (!A32 && a_parts != 1) return fail(EOGP_ERR_INVALID, "gemm: 16-bit A cannot be split");
-  if (A32 && a_parts == 1 && b_parts == 1 && !f16) return launch<0, 1, 1, false>(g, av, bc, s);
-  if (A32 && a_parts == 2 && b_parts == 2 && !f16) return launch<0, 2, 2, false>(g, av, bc, s);
-  if (A32 && a_parts == 2 && b_parts == 1 && !f16) return launch<0, 2, 1, false>(g, av, bc, s);
-  if (A32 && a_parts == 1 && b_parts == 1 && f16) return launch<0, 1, 1, true>(g, av, bc, s);
-  if (A32 && a_parts == 2 && b_parts == 1 && f16) return launch<0, 2, 1, true>(g, av, bc, s);
-  if (!A32 && b_parts == 1 && !f16) return launch<1, 1, 1, false>(g, av, bc, s);
-  if (!A32 && b_parts == 2 && !f16) return launch<1, 1, 2, false>(g, av, bc, s);
-  if (!A32 && b_parts == 1 && f16) return launch<1, 1, 1, true>(g, av, bc, s);
+  if (A32 && a_parts == 1 && b_parts == 1 && !f16) return launch<0, 1, 1, false>(g, b16, s);
+  if (A32 && a_parts == 2 && b_parts == 2 && !f16) return launch<0, 2, 2, false>(g, b16, s);
+  if (A32 && a_parts == 2 && b_parts == 1 && !f16) return launch<0, 2, 1, false>(g, b16, s);
+  if (A32 && a_parts == 1 && b_parts == 1 && f16) return launch<0, 1, 1, true>(g, b16, s);
+  if (A32 && a_parts == 2 && b_parts == 1 && f16) return launch<0, 2, 1, true>(g, b16, s);
+  if (!A32 && b_parts == 1 && !f16) return launch<1, 1, 1, false>(g, b16, s);
+  if (!A32 && b_parts == 2 && !f16) return launch<1, 1, 2, false>(g, b16, s);
+  if (!A32 && b_parts == 1 && f16) return launch<1, 1, 1, true>(g, b16, s);
   return fail(EOGP_ERR_UNSUPPORTED, "gemm: unsupported operand combination");
 }
 
