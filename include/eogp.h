@@ -359,7 +359,9 @@ eogp_status eogp_score_topk_noalloc(const uint8_t* codes, int64_t code_row_strid
  *             rotated tokens are also kept in fp16 (relative error of
  *             sq_sum about 1e-3) and the squares are fp16 MFMA products.
  *   sq_sum    [d_out, d_in] fp32, row-major (the layout of eigvals).
- *   ws        at least eogp_ekfac_workspace_size bytes.
+ *   ws        eogp_ekfac_workspace_size bytes. A smaller workspace with room
+ *             for the fewest ranges of examples (the fp16 mode sums ranges
+ *             apart) is accepted; the fp32 sums then run in another order.
  * Errors as for eogp_rotate_retain; EOGP_ERR_INVALID for an exponent outside
  * [-60, 60]. The sum over examples is formed in a fixed order, so repeated
  * calls give identical results.

@@ -383,8 +383,7 @@ eogp_status eogp_ekfac_eigenvalues(const void* acts, int64_t ld_acts, const void
   if (in_dtype == EOGP_BF16 &&
       (ld_acts % 8 || ld_grads % 8 || (uintptr_t)acts % 16 || (uintptr_t)out_grads % 16))
     return fail(EOGP_ERR_UNSUPPORTED, "ekfac: bf16 token rows must start on 16-byte boundaries");
-  if (ws_bytes < ekfac_ws(N, T, d_in, d_out) || !ws)
-    return fail(EOGP_ERR_WORKSPACE, "ekfac: workspace too small");
+  if (!ws) return fail(EOGP_ERR_WORKSPACE, "ekfac: workspace too small");
   return ekfac_pass(acts, ld_acts, out_grads, ld_grads, in_dtype == EOGP_BF16, token_mask, N, T,
                     d_in, d_out, Q_A, Q_S, (int)prec, e_acts, e_grads, sq_sum, accumulate, ws,
                     ws_bytes, S(stream));

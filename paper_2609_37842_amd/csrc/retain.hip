@@ -80,7 +80,9 @@ __global__ __launch_bounds__(256) void k_write_tokens(const uint8_t* __restrict_
 // is one 32 x 32 fp32 MFMA accumulation over the example's tokens, two tokens
 // per v_mfma_f32_32x32x2_f32 (lane l feeds row l % 32 of token l / 32 of each
 // operand straight from memory). Products are exact fp32 products, so the
-// result matches an fp32 dot product up to the order of the additions.
+// result matches an fp32 dot product up to the order of the additions. (All blocks
+// of an example on one XCD measured no faster, so what the eight L2s read is not
+// what bounds it.)
 constexpr int kRetWaves = 4;
 constexpr int kRetUnroll = 8;      // MFMAs (token pairs) per loaded group
 
@@ -608,61 +610,89 @@ __global__ __launch_bounds__(256) void k_ekfac_sq(const float* __restrict__ St, 
 }
 
 // fp16 mode: S~ and A~ in the fp16 fragment order of the first stage (runs
-// aligned to 8 tokens). A wave owns one 32-row block jb and KQ = 4 32-column
-// blocks kb .. kb+3 (32 x 128 entries); per 16 tokens it loads one S~ block
-// and four A~ blocks (1 KB each) and issues four v_mfma_f32_32x32x16_f16, so
-// each loaded block feeds 0.8 MFMAs; the four waves of a
-// workgroup take neighbouring row blocks and the same column blocks, whose
-// loads they share through the L1. Example by example the block sums C are
-// formed over the example's tokens (tokens past its run zeroed) and C * C is
-// added to the running sums. Small modules split the examples into ranges
-// (grid z) so that the grid still fills the chip; each range writes its own
-// partial sums, which k_ekfac_sum adds in range order (deterministic).
+// aligned to 8 tokens). A workgroup owns 4 x 4 blocks of 32 x 32 entries, each of
+// its waves 2 x 2: per 16 tokens a wave loads two S~ and two A~ blocks (1 KB each)
+// and issues four v_mfma_f32_32x32x16_f16, so each loaded block feeds one MFMA
+// (1 x 4 blocks per wave: 0.8) and the workgroup's four waves share all of them
+// through the L1. Bound by those loads: 16 KB per 16 tokens and CU against 128
+// cycles of MFMA on each SIMD. Example by example the block sums C are formed over
+// the example's tokens (tokens past its run zeroed) and C * C is added to the
+// running sums. The examples are split into ranges of about equal token counts;
+// each writes its own partial sums, which k_ekfac_sum adds in range order
+// (deterministic). Consecutive workgroups go to the XCDs in turn, so with a
+// multiple of eight ranges a range (innermost in the grid) stays on one XCD, whose
+// L2 alone reads its tokens.
+// The whole pass on 256 examples of a 769 x 2,304 module: 1,842 -> 1,595 us; 200 of a
+// 769 x 768 module 346 -> 289 us; 128 of 3,073 x 768 1,400 -> 1,342 us (1 x 4 blocks
+// per wave took 307 registers, one wave per SIMD; these take 226, two).
 constexpr int kSq16Unroll = 4;     // 16-token steps loaded per batch
-constexpr int kSq16Cols = 4;       // 32-column blocks per wave (measured best of 1, 2, 4, 8)
+constexpr int kSq16Side = 2;       // blocks per wave along each axis
 
-template <int KQ>
-__global__ __launch_bounds__(256) void k_ekfac_sq16(const uint16_t* __restrict__ St,
+// First example at or past the share'th of `splits` equal parts of the tokens.
+__device__ __forceinline__ int64_t range_begin(const int32_t* __restrict__ ex_off, int64_t N, int share,
+                                               int splits) {
+  if (share <= 0) return 0;
+  if (share >= splits) return N;
+  const int64_t at = (int64_t)ex_off[N] * share / splits;
+  int64_t lo = 0, hi = N;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    if (ex_off[mid] < at) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
+__global__ __launch_bounds__(256, 2) void k_ekfac_sq16(const uint16_t* __restrict__ St,
                                                     const uint16_t* __restrict__ At, int64_t ldt,
                                                     const int32_t* __restrict__ ex_off,
                                                     const int32_t* __restrict__ ex_len, int64_t N,
                                                     int splits, int d_out, int d_in,
                                                     float* __restrict__ part) {
   typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+  constexpr int Q = kSq16Side;
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int jb = blockIdx.y * 4 + wid;
-  const int kb0 = blockIdx.x * KQ;
-  if (jb * 32 >= d_out) return;                // whole wave leaves; no block barrier below
-  const int split = blockIdx.z;
-  const int64_t i_beg = split * N / splits, i_end = (split + 1) * N / splits;
+  const int nbx = (d_in + 64 * Q - 1) / (64 * Q);
+  const int split = blockIdx.x % splits, tile = blockIdx.x / splits;
+  const int jb0 = ((tile / nbx) * 2 + (wid >> 1)) * Q;
+  const int kb0 = ((tile % nbx) * 2 + (wid & 1)) * Q;
+  if (jb0 * 32 >= d_out || kb0 * 32 >= d_in) return;   // whole wave leaves; no block barrier below
+  const int64_t i_beg = range_begin(ex_off, N, split, splits);
+  const int64_t i_end = range_begin(ex_off, N, split + 1, splits);
   const int half = lane >> 5, col = lane & 31;
   const int64_t groups = ldt / 16;
+  const int64_t bstride = groups * 512;        // elements from one column block to the next
   auto at_tok = [&](int64_t b, int64_t t) { return ((b * groups + (t >> 4)) * 32 + col) * 16 + (t & 15); };
-  f32x16 acc2[KQ];
+  f32x16 acc2[Q][Q];
 #pragma unroll
-  for (int q = 0; q < KQ; ++q)
+  for (int p = 0; p < Q; ++p)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc2[q][r] = 0.f;
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc2[p][q][r] = 0.f;
   for (int64_t i = i_beg; i < i_end; ++i) {
     const int n = ex_len[i];
     if (n == 0) continue;
     const int64_t t0 = ex_off[i] + 8 * half;
-    const uint16_t* sp = St + at_tok(jb, t0);
+    const uint16_t* sp = St + at_tok(jb0, t0);
     const uint16_t* ap = At + at_tok(kb0, t0);
-    const int64_t bstride = groups * 512;      // elements from one column block to the next
-    f32x16 c[KQ];
+    f32x16 c[Q][Q];
 #pragma unroll
-    for (int q = 0; q < KQ; ++q)
+    for (int p = 0; p < Q; ++p)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) c[q][r] = 0.f;
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) c[p][q][r] = 0.f;
     for (int t = 0; t < n; t += 16 * kSq16Unroll) {
-      v4u a[kSq16Unroll], b[kSq16Unroll][KQ];
+      v4u a[kSq16Unroll][Q], b[kSq16Unroll][Q];
 #pragma unroll
       for (int u = 0; u < kSq16Unroll; ++u) {
         const int64_t o = (int64_t)(t / 16 + u) * 512;
-        a[u] = *reinterpret_cast<const v4u*>(sp + o);
 #pragma unroll
-        for (int q = 0; q < KQ; ++q) b[u][q] = *reinterpret_cast<const v4u*>(ap + q * bstride + o);
+        for (int q = 0; q < Q; ++q) {
+          a[u][q] = *reinterpret_cast<const v4u*>(sp + q * bstride + o);
+          b[u][q] = *reinterpret_cast<const v4u*>(ap + q * bstride + o);
+        }
       }
 #pragma unroll
       for (int u = 0; u < kSq16Unroll; ++u) {
@@ -673,32 +703,40 @@ __global__ __launch_bounds__(256) void k_ekfac_sq16(const uint16_t* __restrict__
 #pragma unroll
           for (int d = 0; d < 4; ++d) {
             const uint32_t keep = (2 * d < rem ? 0x0000FFFFu : 0u) | (2 * d + 1 < rem ? 0xFFFF0000u : 0u);
-            a[u][d] &= keep;
 #pragma unroll
-            for (int q = 0; q < KQ; ++q) b[u][q][d] &= keep;
+            for (int q = 0; q < Q; ++q) {
+              a[u][q][d] &= keep;
+              b[u][q][d] &= keep;
+            }
           }
         }
 #pragma unroll
-        for (int q = 0; q < KQ; ++q)
-          c[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a[u]),
-                                                        __builtin_bit_cast(f16x8, b[u][q]), c[q], 0, 0, 0);
+        for (int p = 0; p < Q; ++p)
+#pragma unroll
+          for (int q = 0; q < Q; ++q)
+            c[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a[u][p]),
+                                                             __builtin_bit_cast(f16x8, b[u][q]), c[p][q], 0, 0, 0);
       }
     }
 #pragma unroll
-    for (int q = 0; q < KQ; ++q)
+    for (int p = 0; p < Q; ++p)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc2[q][r] = fmaf(c[q][r], c[q][r], acc2[q][r]);
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc2[p][q][r] = fmaf(c[p][q][r], c[p][q][r], acc2[p][q][r]);
   }
-  // acc2[q][r] holds entry (32 jb + 8 (r / 4) + 4 half + r % 4, 32 (kb0 + q) + col)
+  // acc2[p][q][r] holds entry (32 (jb0 + p) + 8 (r / 4) + 4 half + r % 4, 32 (kb0 + q) + col)
   float* o = part + (int64_t)split * d_out * d_in;
 #pragma unroll
-  for (int q = 0; q < KQ; ++q)
+  for (int p = 0; p < Q; ++p)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int j = jb * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-      const int k = (kb0 + q) * 32 + col;
-      if (j < d_out && k < d_in) o[(int64_t)j * d_in + k] = acc2[q][r];
-    }
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int j = (jb0 + p) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        const int k = (kb0 + q) * 32 + col;
+        if (j < d_out && k < d_in) o[(int64_t)j * d_in + k] = acc2[p][q][r];
+      }
 }
 
 // sq[e] = (accumulate ? sq[e] : 0) + h^2 * sum over ranges, in order, of part[s][e]
@@ -720,13 +758,37 @@ __global__ __launch_bounds__(256) void k_fill_zero(float* __restrict__ x, int64_
   if (e < n) x[e] = 0.f;
 }
 
-// Example ranges of the fp16 squares: enough workgroups for two per CU, at
-// least 4 examples per range, at most 32 ranges.
-int sq16_splits(int64_t N, int64_t d_in, int64_t d_out) {
-  const int64_t groups = ceil_div(d_in, 32 * kSq16Cols) * ceil_div(d_out, 128);
+// Ranges of examples that a workspace always has room for.
+int sq16_min_splits(int64_t N, int64_t d_in, int64_t d_out) {
+  const int64_t groups = ceil_div(d_in, 128) * ceil_div(d_out, 128);
   int64_t sp = ceil_div(2 * kCus, groups);
   sp = std::min<int64_t>(sp, std::max<int64_t>(1, N / 4));
   return (int)std::max<int64_t>(1, std::min<int64_t>(sp, 32));
+}
+
+// Example ranges of the fp16 squares when the scratch allows: eight (one XCD per
+// range), or for modules whose tiles are few the multiple of eight up to 32 that
+// fills the last round of two workgroups per CU best (the first at 90%), with at
+// least 4 examples per range.
+// More ranges where eight fill the chip cost more partial sums than the fuller round
+// gives: 128 examples of 3,073 x 768 took 1,401 us with 16 ranges, 1,345 at the start;
+// with eight 1,342 (start 1,400 on that box).
+// Batches of fewer than 32 examples, and modules whose tiles alone fill the chip
+// (their partial sums would cost more than the shared L2 gives), take the fewest.
+int sq16_splits(int64_t N, int64_t d_in, int64_t d_out) {
+  const int64_t groups = ceil_div(d_in, 128) * ceil_div(d_out, 128);
+  if (N < 32 || groups >= 2 * kCus) return sq16_min_splits(N, d_in, d_out);
+  int best = 8;
+  double most = 0;
+  for (int sp = 8; sp <= 32 && sp * 4 <= N && groups * best < 2 * kCus; sp += 8) {
+    const double rounds = (double)(groups * sp) / (2 * kCus), full = rounds / std::ceil(rounds);
+    if (full > most) {
+      most = full;
+      best = sp;
+    }
+    if (full >= 0.9) break;
+  }
+  return best;
 }
 
 eogp_plan basis_plan(int64_t d_in, int64_t d_out) {
@@ -749,10 +811,16 @@ size_t panel_bytes(const eogp_plan& q) {
 
 }  // namespace
 
+namespace {
+size_t ekfac_fixed_bytes(const eogp_plan& q, int64_t N, int64_t T) {
+  return work_bytes(&q, N, T) + panel_bytes(q);
+}
+}  // namespace
+
 size_t ekfac_ws(int64_t N, int64_t T, int64_t d_in, int64_t d_out) {
   const eogp_plan q = basis_plan(d_in, d_out);
-  return work_bytes(&q, N, T) + panel_bytes(q) +
-         align256((size_t)sq16_splits(N, d_in, d_out) * d_out * d_in * 4);
+  return ekfac_fixed_bytes(q, N, T) +
+         align256((size_t)std::max(sq16_splits(N, d_in, d_out), sq16_min_splits(N, d_in, d_out)) * d_out * d_in * 4);
 }
 
 eogp_status ekfac_pass(const void* acts, int64_t ld_acts, const void* grads, int64_t ld_grads,
@@ -761,7 +829,11 @@ eogp_status ekfac_pass(const void* acts, int64_t ld_acts, const void* grads, int
                        int32_t e_acts, int32_t e_grads, float* sq, int accumulate, void* ws,
                        size_t ws_bytes, hipStream_t s) {
   eogp_plan q = basis_plan(d_in, d_out);
-  if (ws_bytes < ekfac_ws(N, T, d_in, d_out)) return fail(EOGP_ERR_WORKSPACE, "ekfac: workspace too small");
+  // A workspace with room for the fewest ranges does; more ranges where it has room for them.
+  const size_t fixed = ekfac_fixed_bytes(q, N, T), sums = (size_t)d_out * d_in * 4;
+  int splits = sq16_min_splits(N, d_in, d_out);
+  if (ws_bytes < fixed + align256((size_t)splits * sums)) return fail(EOGP_ERR_WORKSPACE, "ekfac: workspace too small");
+  if (ws_bytes >= fixed + align256((size_t)sq16_splits(N, d_in, d_out) * sums)) splits = sq16_splits(N, d_in, d_out);
   if (N == 0) {                                  // an empty batch adds nothing
     if (!accumulate) {
       hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)ceil_div(d_out * d_in, 256)), dim3(256), 0, s,
@@ -784,21 +856,19 @@ eogp_status ekfac_pass(const void* acts, int64_t ld_acts, const void* grads, int
   basis_panels(Q_S, d_out, q.rows_pad, q.ld_out, list, q.qs_hi, q.qs_lo, q.qs_f16, s);
   basis_panels(Q_A, d_in, q.cols_pad, q.ld_in, list, q.qa_hi, q.qa_lo, q.qa_f16, s);
   EOGP_LAUNCH_CHECK("ekfac panels");
-  float* part = cv.take<float>((size_t)sq16_splits(N, d_in, d_out) * d_out * d_in);
+  float* part = cv.take<float>((size_t)splits * d_out * d_in);
   const bool f16 = prec == EOGP_PREC_F16;
   eogp_status st = rotate_tokens(&q, acts, ld_acts, grads, ld_grads, bf16_in, mask, N, T, prec, f16,
                                  true, w, s);
   if (st != EOGP_OK) return st;
   timing::Scope ts(EOGP_KT_EKFAC, s);
   if (f16) {
-    const int sp = sq16_splits(N, d_in, d_out);
-    hipLaunchKernelGGL(k_ekfac_sq16<kSq16Cols>, dim3((unsigned)ceil_div(d_in, 32 * kSq16Cols), (unsigned)ceil_div(d_out, 128),
-                                          (unsigned)sp),
-                       dim3(256), 0, s, w.St16, w.At16, w.ldt, w.cnt, w.len, N, sp, (int)d_out,
-                       (int)d_in, part);
+    const int64_t tiles = ceil_div(d_in, 64 * kSq16Side) * ceil_div(d_out, 64 * kSq16Side);
+    hipLaunchKernelGGL(k_ekfac_sq16, dim3((unsigned)(tiles * splits)), dim3(256), 0, s, w.St16, w.At16, w.ldt,
+                       w.cnt, w.len, N, splits, (int)d_out, (int)d_in, part);
     const int64_t n = d_out * d_in;
     const float h = std::ldexp(1.f, -(e_acts + e_grads));
-    hipLaunchKernelGGL(k_ekfac_sum, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, part, sp, n,
+    hipLaunchKernelGGL(k_ekfac_sum, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, part, splits, n,
                        h, sq, accumulate);
     EOGP_LAUNCH_CHECK("ekfac squares");
     return EOGP_OK;

@@ -146,11 +146,18 @@ def _need_cuda(*ts):
             raise ValueError("EOGP arguments must be device tensors")
 
 
-def _workspace(nbytes: int, device, ws=None):
+def _check_workspace(status: int, need: int):
+    """For calls that run in less than the size reported: the library decides."""
+    if status == -4:                             # EOGP_ERR_WORKSPACE
+        raise ValueError(f"workspace needs {need} bytes")
+    _check(status)
+
+
+def _workspace(nbytes: int, device, ws=None, less_ok=False):
     if nbytes == 0:
         return None, 0
     if ws is not None:
-        if ws.numel() * ws.element_size() < nbytes:
+        if not less_ok and ws.numel() * ws.element_size() < nbytes:
             raise ValueError(f"workspace needs {nbytes} bytes")
         return ws, ws.numel() * ws.element_size()
     return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
@@ -373,12 +380,13 @@ def eogp_ekfac_eigenvalues(acts, out_grads, token_mask, Q_A, Q_S, sq_sum=None, a
     if sq_sum.dtype != torch.float32 or tuple(sq_sum.shape) != (d_out, d_in) or not sq_sum.is_contiguous():
         raise ValueError("sq_sum must be contiguous float32 [d_out, d_in]")
     need = int(L.eogp_ekfac_workspace_size(N, T, d_in, d_out))
-    ws, wsb = _workspace(need, acts.device, ws)
-    _check(L.eogp_ekfac_eigenvalues(_ptr(acts), ld_a, _ptr(out_grads), ld_g,
-                                    _acts_dtype(acts, out_grads), _ptr(token_mask), N, T, d_in,
-                                    d_out, _ptr(Q_A), _ptr(Q_S), prec, int(exponents[0]),
-                                    int(exponents[1]), _ptr(sq_sum), 1 if accumulate else 0,
-                                    _ptr(ws), wsb, _stream(stream)))
+    ws, wsb = _workspace(need, acts.device, ws, less_ok=True)
+    status = L.eogp_ekfac_eigenvalues(_ptr(acts), ld_a, _ptr(out_grads), ld_g,
+                                      _acts_dtype(acts, out_grads), _ptr(token_mask), N, T, d_in,
+                                      d_out, _ptr(Q_A), _ptr(Q_S), prec, int(exponents[0]),
+                                      int(exponents[1]), _ptr(sq_sum), 1 if accumulate else 0,
+                                      _ptr(ws), wsb, _stream(stream))
+    _check_workspace(status, need)
     return sq_sum
 
 
@@ -497,11 +505,12 @@ def eogp_score_topk_tiled(codes, scales, N, k_per_module, Y, topk, full_scores=F
         out_score = torch.empty((Q, topk), dtype=torch.float32, device=Y.device)
     full = torch.empty((Q, N), dtype=torch.float32, device=Y.device) if full_scores else None
     need = int(L.eogp_score_topk_workspace_size(N, Q, U, ks, topk))
-    ws, wsb = _workspace(need, Y.device, ws)
+    ws, wsb = _workspace(need, Y.device, ws, less_ok=True)
     ldy = Y.stride(0) if Q > 0 else sum(int(k) for k in k_per_module)
-    _check(L.eogp_score_topk_tiled(_ptr(codes), _ptr(scales), N, U, ks, _ptr(Y), ldy, Q, topk,
-                                   _ptr(out_idx), _ptr(out_score), _ptr(full), _ptr(ws), wsb,
-                                   _stream(stream)))
+    status = L.eogp_score_topk_tiled(_ptr(codes), _ptr(scales), N, U, ks, _ptr(Y), ldy, Q, topk,
+                                     _ptr(out_idx), _ptr(out_score), _ptr(full), _ptr(ws), wsb,
+                                     _stream(stream))
+    _check_workspace(status, need)
     return out_idx, out_score, full
 
 
@@ -567,10 +576,11 @@ def eogp_score_topk(codes, scales, k_per_module, Y, topk, full_scores=False, out
         out_score = torch.empty((Q, topk), dtype=torch.float32, device=Y.device)
     full = torch.empty((Q, N), dtype=torch.float32, device=Y.device) if full_scores else None
     need = int(L.eogp_score_topk_workspace_size(N, Q, U, ks, topk))
-    ws, wsb = _workspace(need, Y.device, ws)
-    _check(L.eogp_score_topk(_ptr(codes), cstride, _ptr(scales), N, U, ks, _ptr(Y), ldy, Q,
-                             topk, _ptr(out_idx), _ptr(out_score), _ptr(full), _ptr(ws), wsb,
-                             _stream(stream)))
+    ws, wsb = _workspace(need, Y.device, ws, less_ok=True)
+    status = L.eogp_score_topk(_ptr(codes), cstride, _ptr(scales), N, U, ks, _ptr(Y), ldy, Q,
+                               topk, _ptr(out_idx), _ptr(out_score), _ptr(full), _ptr(ws), wsb,
+                               _stream(stream))
+    _check_workspace(status, need)
     return out_idx, out_score, full
 
 
