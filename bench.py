@@ -739,7 +739,7 @@ def olmo_scoring(w, dev, n_queries=None):
     mfma_bound_ms = 4.0 * Q * N * U * k / (INT8_PEAK_TOPS * 1e12) * 1e3
     out = {"workload": w.name + " scoring", "layout": "tiled", "codes": N, "modules": U,
            "bits_per_module": k,
-           "queries": Q, "topk": topk, "queries_per_pass": 16, "passes": passes,
+           "queries": Q, "topk": topk, "queries_per_pass": -(-Q // max(1, passes)), "passes": passes,
            "bytes_per_pass": bytes_per_pass, "ms_per_pass": avg, "hbm_GBps": gbs,
            "peak_GBps": HBM_PEAK_GBS, "frac": gbs / HBM_PEAK_GBS,
            "prep_ms": prep_ms, "merge_ms_total": merge_ms, "job_ms": 1000.0 * total_s,
@@ -794,7 +794,7 @@ def scoring_at_scale(args, dev):
     return {
         "workload": w.name, "layout": "tiled",
         "codes": N, "bits": k, "queries": Q, "topk": topk,
-        "queries_per_pass": 16, "passes": passes,
+        "queries_per_pass": -(-Q // max(1, passes)), "passes": passes,
         "bytes_per_pass": bytes_per_pass,
         "ms_per_pass": avg,
         "hbm_GBps": gbs,
