@@ -544,7 +544,7 @@ inline bool use_buffer_b(const GemmArgs& g) {
 // BT: B is a caller's matrix whose ragged last slice is loaded with bounds checks;
 // its own instance, because the extra code moved the slice loop's registers:
 // 24 examples of 2,048 bf16 tokens of a 5,120 x 5,120 module, 1,790 us without the
-// code, 1,802 us with it in the common instance (same box; now as without it).
+// code, 1,802 us with it in the common instance (same card; now as without it).
 template <int AT, bool F16, bool SC, bool BB, int NWV, bool BT = false>
 __global__ __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(NWV / 4, NWV / 4)))
 void k_gemm_p(KParams kp) {

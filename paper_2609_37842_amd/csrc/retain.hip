@@ -772,7 +772,7 @@ int sq16_min_splits(int64_t N, int64_t d_in, int64_t d_out) {
 // least 4 examples per range.
 // More ranges where eight fill the chip cost more partial sums than the fuller round
 // gives: 128 examples of 3,073 x 768 took 1,401 us with 16 ranges, 1,345 at the start;
-// with eight 1,342 (start 1,400 on that box).
+// with eight 1,342 (1,400 at the start on that card).
 // Batches of fewer than 32 examples, and modules whose tiles alone fill the chip
 // (their partial sums would cost more than the shared L2 gives), take the fewest.
 int sq16_splits(int64_t N, int64_t d_in, int64_t d_out) {
