@@ -1,0 +1,54 @@
+"""Calls that must not cost more than a call with more to do: each test times
+both on the same card, in turn, and compares medians."""
+import statistics
+
+import pytest
+import torch
+
+from paper_2609_37842_amd import eogp as E
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def times(*calls, passes=20, rounds=9):
+    """Median time of one pass of each call, in microseconds."""
+    for f in calls:
+        f()
+    got = [[] for _ in calls]
+    for _ in range(rounds):
+        for f, out in zip(calls, got):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            t0.record()
+            for _ in range(passes):
+                f()
+            t1.record()
+            torch.cuda.synchronize()
+            out.append(t0.elapsed_time(t1) * 1e3 / passes)
+    return [statistics.median(x) for x in got]
+
+
+def random_store(N, k, Q, seed=1):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    codes = torch.randint(0, 256, (N, k // 8), device=DEV, dtype=torch.uint8, generator=g)
+    scales = torch.rand((N, 1), device=DEV, generator=g).add_(0.5).half().view(torch.int16)
+    return codes, scales, torch.randn((Q, k), device=DEV, generator=g)
+
+
+@pytest.mark.parametrize("N,k", [(256, 128), (20000, 128), (20000, 2048)])
+def test_one_query_costs_no_more_than_sixteen(N, k):
+    """Lists of the fifteen queries that do not exist take no selection of their own."""
+    codes, scales, Y = random_store(N, k, 16)
+
+    def call(Q):
+        ws = torch.empty(E.eogp_score_topk_workspace_size(N, Q, [k], 10), dtype=torch.uint8, device=DEV)
+        idx = torch.empty((Q, 10), dtype=torch.int64, device=DEV)
+        top = torch.empty((Q, 10), device=DEV)
+        return lambda: E.eogp_score_topk(codes, scales, [k], Y[:Q], 10, out_idx=idx, out_score=top, ws=ws)
+
+    one, sixteen = times(call(1), call(16))
+    print(f"[times] N={N} k={k}: one query {one:.1f} us, sixteen {sixteen:.1f} us", flush=True)
+    assert one <= sixteen
