@@ -71,3 +71,25 @@ def test_row_major_store_is_read_in_whole_loads():
     rows, tiled = times(*layout_calls(473_050, 6144, 16))
     print(f"[times] 473,050 x 6,144 bits, 16 queries: row-major {rows:.1f} us, tiled {tiled:.1f} us", flush=True)
     assert rows <= 1.4 * tiled
+
+
+def test_short_modules_cost_what_their_bits_cost():
+    """The same bits and dots in one long module and in many short ones: what ends a
+    module (its dots written) is not a chain of waits."""
+    N, Q, topk = 200_000, 16, 10
+    scales = torch.rand((N, 64), device=DEV).add_(0.5).half().view(torch.int16)
+    codes = torch.randint(0, 256, (E.tiled_store_bytes(N, [512] * 64),), device=DEV, dtype=torch.uint8)
+    Y = torch.randn((Q, 64 * 512), device=DEV)
+    idx = torch.empty((Q, topk), dtype=torch.int64, device=DEV)
+    top = torch.empty((Q, topk), device=DEV)
+
+    def call(U):
+        ks = [64 * 512 // U] * U
+        s = scales[:, :U].contiguous()
+        ws = torch.empty(E.eogp_score_topk_workspace_size(N, Q, ks, topk), dtype=torch.uint8, device=DEV)
+        return lambda: E.eogp_score_topk_tiled(codes, s, N, ks, Y, topk, out_idx=idx, out_score=top, ws=ws)
+
+    few, many = times(call(4), call(64))
+    dots = 60 * N * Q * 4                       # bytes that 60 more modules write, and read again
+    print(f"[times] 200,000 x 32,768 bits: 4 modules {few:.1f} us, 64 modules {many:.1f} us", flush=True)
+    assert many <= few + 2 * dots / 6.5e6       # 236 us at 6.5 TB/s (155 measured; as a chain 308)
