@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <string>
 
+#include "chip.h"
 #include "eogp.h"
 
 namespace eogp {
@@ -30,10 +31,6 @@ eogp_status check_hip(hipError_t e, const char* what);
 // per (kernel, device); safe to call from several host threads.
 eogp_status ensure_dynamic_lds(const void* fn, int bytes);
 
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
-inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-
 // Bump allocator over a caller workspace (256-byte aligned slices).
 struct Carve {
   char* base;
@@ -57,8 +54,6 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
 
 constexpr int kWave = 64;
-constexpr int kXcds = 8;        // MI355X: 8 accelerator complex dies, 32 CUs each
-constexpr int kCus = 256;
 
 // fp64 -> fp16 bit pattern, round to nearest even, overflow -> inf (IEEE).
 __device__ __forceinline__ uint16_t f64_to_f16_rne(double x) {

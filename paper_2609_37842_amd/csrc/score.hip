@@ -51,31 +51,19 @@
 #include <utility>
 
 #include "common.h"
+#include "score_plan.h"
 #include "timing.h"
 
 namespace eogp {
 namespace {
 
-constexpr int QB = 16;                 // queries per pass
-constexpr int NW = 8;                  // waves per workgroup
 constexpr int NTHR = NW * 64;
-constexpr int MSPLIT = 16;             // first-level merge workgroups per query
 constexpr int MAX_TOPK = 256;
-
-constexpr int SB = 64;                 // bytes of a row per step
-constexpr int FRAGS = 16;              // plane fragments (1 KB) per step and 16 queries
 constexpr int HALF_U4 = 8 * 64;        // 16-byte slots of a half step's fragments per 16 queries
 
 typedef __attribute__((__vector_size__(16 * sizeof(int)))) int i32x16;
 template <typename T>
 using cptr = const __attribute__((address_space(4))) T*;   // read-only, scalar loads
-
-struct ModInfo {
-  int32_t k;       // bits of the module
-  int32_t coff;    // first coordinate of the module in a query row
-  int32_t boff;    // first byte of the module in a code row
-  int32_t sbase;   // first step of the module
-};
 
 // A shift amount the compiler does not know: a 64-bit shift by it stays one
 // instruction. (Of a shift by a known amount whose crossing bits are masked away
@@ -360,8 +348,6 @@ __device__ __forceinline__ void prune(Cand<NQ, CAP>& cd, int least, int topk) {
     if (__builtin_amdgcn_readfirstlane(cd.cnt[q]) >= least)
       prune_list<CAP>(cd.key[q], cd.idx[q], &cd.cnt[q], &cd.thr[q], topk);
 }
-
-constexpr int MAX_RNG = 64;   // module ranges of the multi-module pass
 
 struct ScoreArgs {
   const uint8_t* codes;
@@ -864,7 +850,6 @@ struct FoldArgs {
   uint32_t* cidx;
 };
 constexpr int FOLD_THR = 256;
-constexpr int FOLD_ROWS = 64;
 constexpr int FOLD_QW = QB / (FOLD_THR / 64);   // queries per wave
 
 template <int CAP, bool N64>
@@ -1073,155 +1058,21 @@ __global__ __launch_bounds__(MRG_THR, 1) void k_merge(const uint64_t* __restrict
   }
 }
 
-// How a call runs: queries per pass / 16 (nqt) and 32-row tiles per wave (rt).
-struct PassCfg {
-  int nqt, rt;
-};
-
-struct Layout {
-  int64_t n_steps = 0;   // steps over all modules
-  int64_t n_groups = 0;  // groups of 16 queries
-  int64_t grid = 0;      // workgroups of the scoring pass
-  int64_t fold_grid = 0; // workgroups of the multi-module fold (0: one module)
-  int n_rng = 1;         // module ranges of the multi-module pass
-  bool n64 = false;      // dots need 64 bits
-  int merge_split = 1;   // first-level merge workgroups per query
-  size_t o_mods = 0, o_fq = 0, o_ys = 0, o_pl = 0, o_ck = 0, o_ci = 0, o_ck2 = 0, o_ci2 = 0,
-         o_part = 0,
-         total = 0;
-};
-
-// Fold lists: 256 candidate slots per query when that leaves room for at least
-// 128 new entries after a prune, else 512.
-inline int fold_cap(int32_t topk) { return topk <= 128 ? 256 : 512; }
-
-// Module ranges of the multi-module pass for n_blocks row blocks: the count
-// that gives the shortest schedule, rounds of units times the steps of a
-// range (a uniform estimate), plus a step per unit for its start and its dots.
-int pick_ranges(int64_t n_blocks, int U, int64_t n_steps) {
-  int best = 1;
-  double best_t = 1e300;
-  const int most = (int)std::min<int64_t>({(int64_t)U, (int64_t)MAX_RNG,
-                                           std::max<int64_t>(1, ceil_div(8 * kCus, std::max<int64_t>(1, n_blocks)))});
-  for (int r = 1; r <= most; ++r) {
-    const double rounds = (double)ceil_div(n_blocks * r, kCus);
-    const double steps = (double)n_steps / U * (double)ceil_div(U, r) + 1.0;
-    if (rounds * steps < best_t * 0.999) {
-      best_t = rounds * steps;
-      best = r;
-    }
-  }
-  return best;
-}
-
-Layout layout(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk, PassCfg c) {
-  Layout L;
-  int64_t kmax = 0;
-  for (int u = 0; u < U; ++u) {
-    L.n_steps += (kmod[u] + 8 * SB - 1) / (8 * SB);
-    kmax = std::max<int64_t>(kmax, kmod[u]);
-  }
-  L.n_groups = (Q + QB - 1) / QB;
-  const int64_t rows = NW * 32 * c.rt;
-  const int64_t n_blocks = (N + rows - 1) / rows;
-  int64_t lists = 0;
-  if (U == 1) {
-    L.grid = std::max<int64_t>(1, std::min<int64_t>(n_blocks, kCus));
-    // lists for the two-tile blocks, whichever block size runs
-    lists = std::max<int64_t>(1, std::min<int64_t>((N + NW * 64 - 1) / (NW * 64), kCus));
-  } else {
-    L.n_rng = pick_ranges(n_blocks, U, L.n_steps);
-    const int64_t units = std::max<int64_t>(1, n_blocks * L.n_rng);
-    L.grid = std::min<int64_t>(units, kCus);
-    if (L.grid >= kXcds) L.grid = L.grid / kXcds * kXcds;
-    L.fold_grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(N, FOLD_ROWS), 2 * kCus));
-    lists = L.fold_grid;
-  }
-  L.n64 = kmax > (1 << 16);     // |n| <= k 2^14 fits 32 bits up to k = 2^16
-  const size_t nq = (size_t)c.nqt * QB;
-  size_t b = 0;
-  auto add = [&](size_t x) { size_t o = b; b = align256(b + x); return o; };
-  L.o_mods = add(sizeof(ModInfo) * U);
-  L.o_fq = add(4 * (size_t)L.n_groups * U * QB);
-  L.o_ys = add(8 * (size_t)L.n_groups * U * QB);
-  L.o_pl = add((size_t)(L.n_groups * L.n_steps) * FRAGS * 1024);
-  L.o_ck = add((size_t)lists * nq * topk * 8);
-  L.o_ci = add((size_t)lists * nq * topk * 4);
-  L.merge_split = (int)std::min<int64_t>(MSPLIT, std::max<int64_t>(1, lists / 8));
-  L.o_ck2 = add((size_t)L.merge_split * nq * topk * 8);
-  L.o_ci2 = add((size_t)L.merge_split * nq * topk * 4);
-  L.o_part = add(U > 1 ? (size_t)U * nq * (size_t)N * (L.n64 ? 8 : 4) : 0);
-  add(16);             // (unused; part of the size that callers have stored and limits count)
-  L.total = b;
-  return L;
-}
-
-// Queries per pass and tiles per wave.
-// 32 queries per pass (nqt = 2) whenever there are more than 16: a pass then
-// reads the store and expands its bits once for twice the MFMAs (1,048,576 codes
-// of 16,384 bits: 0.85 ms per 32 queries against 0.89 ms per 16 before). Not for
-// top-k over 128 (32 lists of more than 256 slots do not fit LDS beside the
-// planes), for dots in 64 bits, nor where the workspace is too small for it:
-// its candidate lists and dots are twice as many, so `ws_bytes` that hold the
-// 16-query layout only get the 16-query pass, with the same results.
-// Four tiles per wave (1,024-row blocks) halve the fragment reads per MFMA and
-// the planes read per code byte (4,194,304 codes, 16 queries: the pass 2.5 -> 1.9
-// ms with it and the requests that run on across blocks); two (512 rows) where
-// the blocks' last round would be emptier: rounds x (rows + a fixed part of a
-// block).
-PassCfg choose_cfg(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk, size_t ws_bytes) {
-  int64_t kmax = 0;
-  for (int u = 0; u < U; ++u) kmax = std::max<int64_t>(kmax, kmod[u]);
-  const bool n64 = kmax > (1 << 16);
-  PassCfg c;
-  c.rt = 2;
-  c.nqt = Q > QB && topk <= 128 && !n64 ? 2 : 1;
-  if (c.nqt == 2 && layout(N, Q, U, kmod, topk, c).total > ws_bytes) c.nqt = 1;
-  if (n64) return c;
-  if (U == 1) {
-    auto rounds = [&](int rt) { return (double)ceil_div(std::max<int64_t>(1, ceil_div(N, NW * 32 * rt)), kCus); };
-    if (rounds(4) * 4.2 < rounds(2) * 2.4) c.rt = 4;
-  } else if (N >= (int64_t)NW * 128 * 24) {
-    c.rt = 4;
-  }
-  return c;
-}
-
-// Module ranges of the multi-module pass: n_rng consecutive ranges of
-// roughly equal step counts, each at least one module (one pass over the
-// module sizes, no host allocation).
-void module_ranges(const int64_t* kmod, int U, int64_t n_steps, int n_rng, int32_t* rng) {
-  auto steps = [&](int u) { return (kmod[u] + 8 * SB - 1) / (8 * SB); };
-  rng[0] = 0;
-  int v = 1;                   // candidate start of the next range
-  int64_t base = steps(0);     // first step of module v
-  for (int r = 1; r < n_rng; ++r) {
-    if (v <= rng[r - 1]) {     // range r - 1 keeps at least one module
-      base += steps(v);
-      ++v;
-    }
-    const int64_t target = (n_steps * r + n_rng / 2) / n_rng;
-    const int v_max = U - (n_rng - r);     // leaves a module for each later range
-    while (v < v_max && base < target) {
-      base += steps(v);
-      ++v;
-    }
-    rng[r] = v;
-  }
-  rng[n_rng] = U;
-}
-
 // One pass of nqt groups; MODE as in k_score.
 template <int MODE, bool TILED>
 void launch_pass(int nqt, int rt, dim3 gd, const ScoreArgs& a, hipStream_t s) {
   const dim3 bd(NTHR);
   if constexpr (MODE == 2 || MODE == 3) {
     hipLaunchKernelGGL((k_score<1, 2, 2, MODE, 512, TILED>), gd, bd, 0, s, a);
-  } else if (nqt == 2) {
-    if (rt == 4) hipLaunchKernelGGL((k_score<2, 4, 1, MODE, 256, TILED>), gd, bd, 0, s, a);
-    else hipLaunchKernelGGL((k_score<2, 2, 1, MODE, 256, TILED>), gd, bd, 0, s, a);
   } else {
-    if (rt == 4) hipLaunchKernelGGL((k_score<1, 4, 2, MODE, 512, TILED>), gd, bd, 0, s, a);
+    if constexpr (TILED) {   // (row-major stores take two tiles per wave)
+      if (rt == 4) {
+        if (nqt == 2) hipLaunchKernelGGL((k_score<2, 4, 1, MODE, 256, true>), gd, bd, 0, s, a);
+        else hipLaunchKernelGGL((k_score<1, 4, 2, MODE, 512, true>), gd, bd, 0, s, a);
+        return;
+      }
+    }
+    if (nqt == 2) hipLaunchKernelGGL((k_score<2, 2, 1, MODE, 256, TILED>), gd, bd, 0, s, a);
     else hipLaunchKernelGGL((k_score<1, 2, 2, MODE, 512, TILED>), gd, bd, 0, s, a);
   }
 }
@@ -1232,12 +1083,12 @@ int32_t score_max_topk() { return MAX_TOPK; }
 
 // The least workspace a call runs with: the 16-query layout.
 size_t score_ws_min(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk) {
-  return layout(N, Q, U, kmod, topk, PassCfg{1, 2}).total;
+  return score_layout(N, Q, U, kmod, topk, PassCfg{1, 2}).total;
 }
 // The workspace of the pass that choose_cfg prefers.
 size_t score_ws(int64_t N, int64_t Q, int32_t U, const int64_t* kmod, int32_t topk) {
-  const PassCfg c = choose_cfg(N, Q, U, kmod, topk, ~size_t(0));
-  return std::max(score_ws_min(N, Q, U, kmod, topk), layout(N, Q, U, kmod, topk, c).total);
+  const PassCfg c = choose_cfg(N, Q, U, kmod, topk, true, ~size_t(0));
+  return std::max(score_ws_min(N, Q, U, kmod, topk), score_layout(N, Q, U, kmod, topk, c).total);
 }
 
 template <bool TILED>
@@ -1245,8 +1096,8 @@ eogp_status score_topk_impl(const uint8_t* codes, int64_t cstride, const uint16_
                             int64_t N, int32_t U, const int64_t* kmod, const float* Y, int64_t ldy,
                             int64_t Q, int32_t topk, int64_t* out_idx, float* out_score,
                             float* full, void* ws, size_t ws_bytes, hipStream_t s) {
-  const PassCfg cfg = choose_cfg(N, Q, U, kmod, topk, ws_bytes);
-  const Layout L = layout(N, Q, U, kmod, topk, cfg);
+  const PassCfg cfg = choose_cfg(N, Q, U, kmod, topk, TILED, ws_bytes);
+  const ScoreLayout L = score_layout(N, Q, U, kmod, topk, cfg);
   if (ws_bytes < L.total) return fail(EOGP_ERR_WORKSPACE, "score_topk: workspace too small");
   if (Q == 0) return EOGP_OK;
   char* base = static_cast<char*>(ws);

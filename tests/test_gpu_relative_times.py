@@ -92,4 +92,22 @@ def test_short_modules_cost_what_their_bits_cost():
     few, many = times(call(4), call(64))
     dots = 60 * N * Q * 4                       # bytes that 60 more modules write, and read again
     print(f"[times] 200,000 x 32,768 bits: 4 modules {few:.1f} us, 64 modules {many:.1f} us", flush=True)
-    assert many <= few + 2 * dots / 6.5e6       # 236 us at 6.5 TB/s (155 measured; as a chain 308)
+    assert many <= few + 2 * dots / 4e6         # 384 us at 4 TB/s (301 measured; as a chain 487)
+
+
+def test_a_quarter_more_codes_cost_no_second_round():
+    """Two modules: 25,600 codes fit the same round of workgroups as 20,480."""
+    Q, topk, ks = 16, 10, [8192, 8192]
+    Y = torch.randn((Q, sum(ks)), device=DEV)
+    idx = torch.empty((Q, topk), dtype=torch.int64, device=DEV)
+    top = torch.empty((Q, topk), device=DEV)
+
+    def call(N):
+        codes = torch.randint(0, 256, (E.tiled_store_bytes(N, ks),), device=DEV, dtype=torch.uint8)
+        scales = torch.rand((N, 2), device=DEV).add_(0.5).half().view(torch.int16)
+        ws = torch.empty(E.eogp_score_topk_workspace_size(N, Q, ks, topk), dtype=torch.uint8, device=DEV)
+        return lambda: E.eogp_score_topk_tiled(codes, scales, N, ks, Y, topk, out_idx=idx, out_score=top, ws=ws)
+
+    less, more = times(call(20_480), call(25_600))
+    print(f"[times] 2 x 8,192 bits: 20,480 codes {less:.1f} us, 25,600 codes {more:.1f} us", flush=True)
+    assert more <= 1.25 * less
