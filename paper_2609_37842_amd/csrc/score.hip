@@ -944,7 +944,9 @@ __global__ __launch_bounds__(FOLD_THR) void k_score_fold(FoldArgs a) {
 // workgroup per query merges those into the sorted top-k (FINAL). Each of the
 // four waves selects the top-k of its share, up to 512 entries at a time in
 // registers (wave_select), then the first wave selects among the four: no
-// barrier but one between the two. Only the final top-k is put in order. (Before, a
+// barrier but one between the two, and no more slots than topk per wave to look
+// through (of 256 each, a merge of 24 lists of 10 took 13.1 + 8.6 us, now 10.1 +
+// 7.4). Only the final top-k is put in order. (Before, a
 // bitonic sort of up to 1,024 entries by the whole workgroup per 512 entries,
 // one barrier per exchange stage: 49 + 46 us for the two levels at 256 lists of
 // 100 for 16 queries, now 21 + 25 us for 32.)
@@ -1022,10 +1024,10 @@ __global__ __launch_bounds__(MRG_THR, 1) void k_merge(const uint64_t* __restrict
   if ((tid & 63) == 0) ml.cnt[wid] = mine;
   __syncthreads();
   if (wid == 0) {
-    // the other waves' lists, as one row of MRG_W - 1 lists of MAX_TOPK slots
-    const int c = wave_topk((MRG_W - 1) * MAX_TOPK, topk, ml.key[0], ml.idx[0], mine,
+    // the other waves' lists, as one row of MRG_W - 1 lists of topk slots
+    const int c = wave_topk((MRG_W - 1) * topk, topk, ml.key[0], ml.idx[0], mine,
                             [&](int e, uint64_t& k, uint32_t& id) {
-                              const int w = 1 + e / MAX_TOPK, at = e % MAX_TOPK;
+                              const int l = (int)((uint32_t)e / (uint32_t)topk), w = 1 + l, at = e - l * topk;
                               k = ml.key[w][at];
                               id = at < ml.cnt[w] ? ml.idx[w][at] : 0xFFFFFFFFu;
                             });

@@ -81,6 +81,15 @@ def test_score_ties_and_infinite_scales(Q, topk):
     check(codes, scales, [512], Y, topk, False)
 
 
+@pytest.mark.parametrize("topk", [1, 2, 63, 64, 65, 127, 170, 171, 256])
+@pytest.mark.parametrize("N,ks", [(9000, [512]), (1500, [512] * 8)])
+def test_score_merge_sizes(N, ks, topk):
+    """The merge's list of the other waves' entries ends inside, at and past one round
+    of 512 (3 topk entries beside the topk kept)."""
+    codes, scales, Y = store(N, ks, 3, topk)
+    check(codes, scales, ks, Y, topk, True)
+
+
 @pytest.mark.parametrize("ks", [[1024], [512, 512]])
 def test_score_workspace_of_the_16_query_layout(ks):
     """A workspace too small for the 32-query pass runs the 16-query one, with
