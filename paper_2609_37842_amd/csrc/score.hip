@@ -573,12 +573,15 @@ void k_score(ScoreArgs a) {
     // y_int come as two scalar loads of 64 bytes and a select by arithmetic: a
     // select between two loads becomes one load per lane and sum, each waiting
     // for every request and store before it (30 modules of up to 1,536 bits,
-    // 694,444 codes, one query: the pass 960 us, now 703).
+    // 694,444 codes, one query: the pass 960 us, now 703). Pairs of queries past the
+    // last are not written (76 modules of 256 bits, 285,916 codes, one query: the
+    // call 1,004 us with them, 606 without).
     auto fold_module = [&]() __attribute__((always_inline)) {
       const int64_t upper = -(int64_t)hg;
 #pragma unroll
       for (int qt = 0; qt < NQT; ++qt) {
         const int64_t mo = ((a.grp + qt) * a.U + wc.u) * QB;
+        const int nq = (int)std::min<int64_t>(QB, a.Q - (a.grp + qt) * QB);   // queries of the group
         int64_t ys[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -588,13 +591,21 @@ void k_score(ScoreArgs a) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
           const int64_t row = row_of(wc.blk, rt);
+          auto put = [&](int i) __attribute__((always_inline)) {   // query q0 + 4 hg of the group
+            const int q0 = 8 * (i >> 2) + (i & 3);
+            const int64_t o = ((int64_t)wc.u * NQ + QB * qt + q0 + 4 * hg) * a.N + row;
+            const int64_t nn = dot(rt, qt, i, ys[i]);
+            if constexpr (MODE == 1) static_cast<int32_t*>(a.part)[o] = (int32_t)nn;
+            else static_cast<int64_t*>(a.part)[o] = nn;
+          };
           if (row < a.N) {
+            if (nq == QB) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-              const int q = QB * qt + 8 * (i >> 2) + (i & 3) + 4 * hg;   // of the pass
-              const int64_t o = ((int64_t)wc.u * NQ + q) * a.N + row, nn = dot(rt, qt, i, ys[i]);
-              if constexpr (MODE == 1) static_cast<int32_t*>(a.part)[o] = (int32_t)nn;
-              else static_cast<int64_t*>(a.part)[o] = nn;
+              for (int i = 0; i < 8; ++i) put(i);
+            } else {
+#pragma unroll
+              for (int i = 0; i < 8; ++i)
+                if (8 * (i >> 2) + (i & 3) < nq) put(i);           // (uniform)
             }
           }
         }
@@ -859,6 +870,8 @@ __global__ __launch_bounds__(FOLD_THR) void k_score_fold(FoldArgs a) {
   const int q0 = __builtin_amdgcn_readfirstlane((tid >> 6) * FOLD_QW);   // wave-uniform
   const int64_t grp = a.grp + blockIdx.y;
   const cptr<int32_t> cfq = (cptr<int32_t>)(a.fq);
+  // this wave's last query among its four (negative: it has none)
+  const int last_q = (int)std::min<int64_t>(FOLD_QW, a.Q - (grp * QB + q0)) - 1;
   if (tid < QB) {
     cd.cnt[tid] = 0;
     cd.thr[tid] = 0ull;
@@ -875,13 +888,14 @@ __global__ __launch_bounds__(FOLD_THR) void k_score_fold(FoldArgs a) {
     double sc[FOLD_QW];
 #pragma unroll
     for (int j = 0; j < FOLD_QW; ++j) sc[j] = 0.0;
+    // (queries past the last have no dots: their place in the wave reads those of its last)
 #pragma unroll 4
-    for (int u = 0; u < a.U; ++u) {
+    for (int u = 0; u < (last_q < 0 ? 0 : a.U); ++u) {
       const double sv = (double)f16_bits_to_f32(a.scales[rowc * a.U + u]);
       const int64_t mo = (grp * a.U + u) * QB + q0;
 #pragma unroll
       for (int j = 0; j < FOLD_QW; ++j) {
-        const int64_t o = ((int64_t)u * a.nq + blockIdx.y * QB + q0 + j) * a.N + rowc;
+        const int64_t o = ((int64_t)u * a.nq + blockIdx.y * QB + q0 + min(j, last_q)) * a.N + rowc;
         const int64_t nn = N64 ? p64[o] : (int64_t)p32[o];
         sc[j] += ldexp(sv * (double)nn, -cfq[mo + j]);
       }

@@ -111,3 +111,22 @@ def test_a_quarter_more_codes_cost_no_second_round():
     less, more = times(call(20_480), call(25_600))
     print(f"[times] 2 x 8,192 bits: 20,480 codes {less:.1f} us, 25,600 codes {more:.1f} us", flush=True)
     assert more <= 1.25 * less
+
+
+def test_one_query_writes_no_dots_of_the_other_fifteen():
+    """Several short modules, where the dots between pass and fold are most of the traffic."""
+    N, U, topk = 200_000, 30, 10
+    ks = [512] * U
+    codes = torch.randint(0, 256, (E.tiled_store_bytes(N, ks),), device=DEV, dtype=torch.uint8)
+    scales = torch.rand((N, U), device=DEV).add_(0.5).half().view(torch.int16)
+    Y = torch.randn((16, sum(ks)), device=DEV)
+
+    def call(Q):
+        ws = torch.empty(E.eogp_score_topk_workspace_size(N, Q, ks, topk), dtype=torch.uint8, device=DEV)
+        idx = torch.empty((Q, topk), dtype=torch.int64, device=DEV)
+        top = torch.empty((Q, topk), device=DEV)
+        return lambda: E.eogp_score_topk_tiled(codes, scales, N, ks, Y[:Q], topk, out_idx=idx, out_score=top, ws=ws)
+
+    one, sixteen = times(call(1), call(16))
+    print(f"[times] 30 x 512 bits, 200,000 codes: one query {one:.1f} us, sixteen {sixteen:.1f} us", flush=True)
+    assert one <= 0.8 * sixteen
