@@ -392,7 +392,9 @@ __device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>,
 // TILED: the store is in the tiled layout (see eogp_sign_pack_tiled): each
 // wave's 32-row tile and step is one 2 KB block whose bytes are already in
 // lane order, each half a contiguous 1 KB; else rows are row-major.
-template <int NQT, int RT, int NCLS, int MODE, int CAP, bool TILED>
+// WHOLE (row-major): the 64 bytes of a row that a step takes are requested together,
+// a step ahead, not 32 bytes at a time.
+template <int NQT, int RT, int NCLS, int MODE, int CAP, bool TILED, bool WHOLE = false>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_score(ScoreArgs a) {
   constexpr bool MULTI = MODE == 1 || MODE == 2;
@@ -502,34 +504,41 @@ void k_score(ScoreArgs a) {
             for (int r = 0; r < 16; ++r) acc[rt][qt][w][r] = 0;
     };
     clear_acc();
-    uint4 cw[2][RT];      // code words of the two halves, requested one step ahead
-    i32x4 pw[NQT];        // this thread's share of the next half's plane fragments
+    // Code words of the two halves of a step: each half requested again as soon as
+    // it is used, or (WHOLE) both together into nx, a step ahead.
+    uint4 cw[2][RT];
+    uint4 nx[2][WHOLE ? RT : 1];
+    // this thread's share of the next half's plane fragments (WHOLE: of each half's next)
+    i32x4 pw[WHOLE ? 2 : 1][NQT];
     uint32_t s16[RT];     // one module: the rows' scales
 
-    // Half H of the loads' step: the plane fragments (staged at the end of the
-    // next half) before the code words (used after it), in the order they are
-    // consumed, as the load counter completes in order. Row-major rows whose
-    // module ends inside the half (k_u a multiple of 64 bits): each lane reads
-    // its 16 bytes as two pieces of 8, those outside the module from readable
-    // bytes instead (the first piece, or the store's first 8 bytes): the planes
-    // are zero there, so the loaded words are used as they are.
-    auto load_half = [&](auto half_c) __attribute__((always_inline)) {
+    // Half H of the loads' step: the plane fragments (staged at the end of the next
+    // half) before the code words (used after it), in the order they are
+    // consumed, as the load counter completes in order.
+    auto load_planes = [&](auto half_c) __attribute__((always_inline)) {
       constexpr int H = decltype(half_c)::value;
 #pragma unroll
       for (int qt = 0; qt < NQT; ++qt)
-        pw[qt] = reinterpret_cast<const i32x4*>(
+        pw[WHOLE ? H : 0][qt] = reinterpret_cast<const i32x4*>(
             a.planes)[((((int64_t)a.grp + qt) * a.n_steps + wl.s_lo + wl.s) * FRAGS + 8 * H) * 64 + tid];
+    };
+    // Row-major rows whose module ends inside the half (k_u a multiple of 64
+    // bits): each lane reads its 16 bytes as two pieces of 8, those outside the
+    // module from readable bytes instead (the first piece, or the store's first
+    // 8 bytes): the planes are zero there, so the loaded words are used as they are.
+    auto load_codes = [&](auto half_c, uint4 (&to)[RT]) __attribute__((always_inline)) {
+      constexpr int H = decltype(half_c)::value;
       if constexpr (TILED) {
         const int64_t so = (int64_t)wl.s * 2048 + H * 1024;
         const uint32_t lo = (uint32_t)lane * 16;
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) cw[H][rt] = *reinterpret_cast<const uint4*>(lrow[rt] + so + lo);
+        for (int rt = 0; rt < RT; ++rt) to[rt] = *reinterpret_cast<const uint4*>(lrow[rt] + so + lo);
       } else {
         const int at = SB * wl.sl + 32 * H + 16 * hg;           // within the module's bytes
         const int64_t pos = (int64_t)wl.boff + at;              // within the row
         if (SB * wl.sl + 32 * H + 32 <= wl.kbytes) {            // uniform
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt) cw[H][rt] = *reinterpret_cast<const uint4*>(lrow[rt] + pos);
+          for (int rt = 0; rt < RT; ++rt) to[rt] = *reinterpret_cast<const uint4*>(lrow[rt] + pos);
         } else {
           const int have = wl.kbytes - at;                      // multiple of 8
 #pragma unroll
@@ -537,7 +546,7 @@ void k_score(ScoreArgs a) {
             const uint8_t* p0 = have >= 8 ? lrow[rt] + pos : a.codes;
             const uint8_t* p1 = have >= 16 ? lrow[rt] + pos + 8 : p0;
             const uint2 v0 = *reinterpret_cast<const uint2*>(p0), v1 = *reinterpret_cast<const uint2*>(p1);
-            cw[H][rt] = make_uint4(v0.x, v0.y, v1.x, v1.y);
+            to[rt] = make_uint4(v0.x, v0.y, v1.x, v1.y);
           }
           // keeps the two branches apart: merged, the 16-byte loads of whole
           // halves became one of 8 bytes and two of 4 each (473,050 rows of
@@ -549,7 +558,8 @@ void k_score(ScoreArgs a) {
     auto stage = [&](auto half_c) __attribute__((always_inline)) {
       constexpr int H = decltype(half_c)::value;
 #pragma unroll
-      for (int qt = 0; qt < NQT; ++qt) *reinterpret_cast<i32x4*>(&sP[H][qt * HALF_U4 + tid]) = pw[qt];
+      for (int qt = 0; qt < NQT; ++qt)
+        *reinterpret_cast<i32x4*>(&sP[H][qt * HALF_U4 + tid]) = pw[WHOLE ? H : 0][qt];
     };
     // the loads' walk moves on, into the next unit after the last step of this
     // one (past the last unit it stays, and its last step is read again, unused)
@@ -661,12 +671,41 @@ void k_score(ScoreArgs a) {
     constexpr std::integral_constant<int, 0> H0{};
     constexpr std::integral_constant<int, 1> H1{};
 
-    // prologue: step 0 requested, its first half staged
+    auto load_half = [&](auto half_c) __attribute__((always_inline)) {
+      load_planes(half_c);
+      load_codes(half_c, cw[decltype(half_c)::value]);
+    };
+    // WHOLE: the next step's code words take their place, and the one after it is
+    // requested. The copies are kept in front of the requests: made at the loop's
+    // end instead, they wait for what was just requested.
+    auto turn_over = [&]() __attribute__((always_inline)) {
+      if constexpr (WHOLE) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            cw[h][rt] = nx[h][rt];
+            asm volatile("" : "+v"(cw[h][rt].x), "+v"(cw[h][rt].y), "+v"(cw[h][rt].z), "+v"(cw[h][rt].w));
+          }
+        advance_loads();
+        load_planes(H0);
+        load_codes(H0, nx[0]);
+        load_codes(H1, nx[1]);
+      }
+    };
+
+    // prologue: step 0 requested (WHOLE: step 1's code words and first planes too),
+    // its first half staged
     load_unit(u_first);
     load_half(H0);
     stage(H0);
     load_half(H1);
     advance_loads();
+    if constexpr (WHOLE) {
+      load_planes(H0);
+      load_codes(H0, nx[0]);
+      load_codes(H1, nx[1]);
+    }
     __syncthreads();
     for (int64_t unit = u_first; unit < q_end; unit += u_step) {
       open_unit(wc, unit);
@@ -677,15 +716,18 @@ void k_score(ScoreArgs a) {
       for (int s = 0; s < wc.n; ++s) {
         half_step(H0);
         stage(H1);
-        load_half(H0);
+        if constexpr (WHOLE) load_planes(H1);
+        else load_half(H0);
         __syncthreads();
         half_step(H1);
         stage(H0);                     // the next step's (or the next unit's first) half
-        load_half(H1);                 // (before the stores, which the next waits would include)
+        if constexpr (WHOLE) turn_over();
+        else load_half(H1);
+        // (after the requests: the next waits would include its stores)
         if (MULTI && wc.sl == wc.nst - 1) fold_module();
         __syncthreads();
         next_step(wc);
-        advance_loads();
+        if constexpr (!WHOLE) advance_loads();
       }
       if constexpr (!MULTI) {
         // candidates of this block. The opaque copy of the lane half keeps the
@@ -1085,6 +1127,17 @@ void launch_pass(int nqt, int rt, dim3 gd, const ScoreArgs& a, hipStream_t s) {
       if (rt == 4) {
         if (nqt == 2) hipLaunchKernelGGL((k_score<2, 4, 1, MODE, 256, true>), gd, bd, 0, s, a);
         else hipLaunchKernelGGL((k_score<1, 4, 2, MODE, 512, true>), gd, bd, 0, s, a);
+        return;
+      }
+    }
+    // Row-major rows a multiple of 8 KB apart: lines of a row fall into few sets of the
+    // L2 and are gone before the step's second half asks again (48 modules of 8,192 bits,
+    // 20,000 codes: 1.40 GB fetched by halves, 0.87 at once), so whole steps are
+    // requested; other rows by halves, which keeps more of the wait covered.
+    if constexpr (MODE == 1 && !TILED) {
+      if (a.cstride % 8192 == 0) {
+        if (nqt == 2) hipLaunchKernelGGL((k_score<2, 2, 1, MODE, 256, false, true>), gd, bd, 0, s, a);
+        else hipLaunchKernelGGL((k_score<1, 2, 2, MODE, 512, false, true>), gd, bd, 0, s, a);
         return;
       }
     }

@@ -130,3 +130,22 @@ def test_one_query_writes_no_dots_of_the_other_fifteen():
     one, sixteen = times(call(1), call(16))
     print(f"[times] 30 x 512 bits, 200,000 codes: one query {one:.1f} us, sixteen {sixteen:.1f} us", flush=True)
     assert one <= 0.8 * sixteen
+
+
+def test_rows_a_power_of_two_apart_cost_little_more():
+    """Row-major rows 16 KB apart (16 modules of 8,192 bits) against rows 64 bytes more."""
+    N, U, Q, topk = 20_000, 16, 4, 10
+    ks = [8192] * U
+    scales = torch.rand((N, U), device=DEV).add_(0.5).half().view(torch.int16)
+    Y = torch.randn((Q, sum(ks)), device=DEV)
+    ws = torch.empty(E.eogp_score_topk_workspace_size(N, Q, ks, topk), dtype=torch.uint8, device=DEV)
+    idx = torch.empty((Q, topk), dtype=torch.int64, device=DEV)
+    top = torch.empty((Q, topk), device=DEV)
+
+    def call(pad):
+        codes = torch.randint(0, 256, (N, 1024 * U + pad), device=DEV, dtype=torch.uint8)[:, :1024 * U]
+        return lambda: E.eogp_score_topk(codes, scales, ks, Y, topk, out_idx=idx, out_score=top, ws=ws)
+
+    even, odd = times(call(0), call(64))
+    print(f"[times] 16 x 8,192 bits row-major: 16 KB apart {even:.1f} us, 64 bytes more {odd:.1f} us", flush=True)
+    assert even <= 1.25 * odd

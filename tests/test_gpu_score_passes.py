@@ -69,6 +69,25 @@ def test_score_module_ends_inside_a_step(N, ks, Q):
     check(codes, scales, ks, Y, 7, False)
 
 
+@pytest.mark.parametrize("ks", [[320, 64, 704], [512, 1024], [1024, 64, 64, 576, 512, 448]])
+@pytest.mark.parametrize("Q", [5, 16, 33])
+@pytest.mark.parametrize("stride", [8192, 16384, 8192 + 8])
+def test_score_rows_far_apart(ks, Q, stride):
+    """Rows a multiple of 8 KB apart are requested a whole step at a time, others by halves;
+    what lies between the rows is not read into any score."""
+    N = 1100
+    codes, scales, Y = store(N, ks, Q, stride + Q)
+    wide = torch.randint(0, 256, (N, stride), device=DEV, dtype=torch.uint8)
+    rows = wide[:, :sum(ks) // 8]
+    rows.copy_(d(codes))
+    got = E.eogp_score_topk(rows, d(scales.view(np.int16)), ks, d(Y), 9, full_scores=True)
+    torch.cuda.synchronize()
+    ref = O.score(codes, scales.view(np.uint16), ks, Y)
+    oi, ov = O.topk(ref, 9)
+    assert np.array_equal(got[2].cpu().numpy(), ref.astype(np.float32))
+    assert np.array_equal(got[0].cpu().numpy(), oi) and np.array_equal(got[1].cpu().numpy(), ov)
+
+
 @pytest.mark.parametrize("Q,topk", [(16, 256), (32, 128), (7, 1)])
 def test_score_ties_and_infinite_scales(Q, topk):
     """Few distinct rows (every list fills with equal keys; the smaller index
