@@ -9,8 +9,10 @@ namespace {
 
 // One workgroup (4 waves) per row, HBM-bound. Wave w takes the 256-coordinate
 // chunks w, w + 4, ...; each lane loads four consecutive coordinates (16 bytes, at
-// any element) of eight chunks before it uses the first, so a row of up to 8,192
-// coordinates is in flight at once. A lane's four signs are a nibble; eight lanes
+// any element) of UNR chunks before it uses the first: eight, so a row of up to
+// 8,192 coordinates is in flight at once; as few as hold a shorter row, because every
+// chunk past its end still costs its bounds checks (20,000 rows of 64: 32.9 us with
+// eight chunks, 14.9 with one). A lane's four signs are a nibble; eight lanes
 // combine theirs by DPP into four bytes of the least-significant-bit-first code
 // (coordinate 4 l + c of a chunk is bit c of lane l's nibble). |x| is summed in
 // fp64 (per lane, then a fixed butterfly, then the four waves in order) and the
@@ -23,7 +25,6 @@ namespace {
 // (tile * steps_row + s), 16-byte piece p (bytes 16p .. 16p+15) at block
 // offset (p % 2) * 1024 + ((p / 2) * 32 + r) * 16: the order in which the
 // scoring pass's wave lanes take them (k a multiple of 512).
-constexpr int kPackUnroll = 8;
 typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // OR over the eight lanes 8 i .. 8 i + 7, in every one of them.
@@ -34,7 +35,7 @@ __device__ __forceinline__ uint32_t or_lanes8(uint32_t x) {
   return x;
 }
 
-template <bool TILED>
+template <bool TILED, int UNR>
 __global__ __launch_bounds__(256) void k_sign_pack(const float* __restrict__ X, int64_t ldx,
                                                    int64_t N, int64_t k,
                                                    uint8_t* __restrict__ codes, int64_t cstride,
@@ -50,10 +51,10 @@ __global__ __launch_bounds__(256) void k_sign_pack(const float* __restrict__ X, 
   uint8_t* tb = codes + ((grow >> 5) * steps_row + step0) * 2048 + (grow & 31) * 16;
   const int64_t nchunk = (k + 255) >> 8, nbytes = (k + 7) >> 3;
   double acc = 0.0;
-  for (int64_t ch0 = wid; ch0 < nchunk; ch0 += 4 * kPackUnroll) {
-    f4_any v[kPackUnroll];
+  for (int64_t ch0 = wid; ch0 < nchunk; ch0 += 4 * UNR) {
+    f4_any v[UNR];
 #pragma unroll
-    for (int u = 0; u < kPackUnroll; ++u) {
+    for (int u = 0; u < UNR; ++u) {
       const int64_t c0 = (ch0 + 4 * u) * 256 + 4 * lane;
       if (TILED || c0 + 4 <= k) {
         if (c0 < k) v[u] = *reinterpret_cast<const f4_any*>(x + c0);
@@ -64,7 +65,7 @@ __global__ __launch_bounds__(256) void k_sign_pack(const float* __restrict__ X, 
       }
     }
 #pragma unroll
-    for (int u = 0; u < kPackUnroll; ++u) {
+    for (int u = 0; u < UNR; ++u) {
       const int64_t ch = ch0 + 4 * u;
       if (ch >= nchunk) break;                     // uniform across the wave
       const int64_t c0 = ch * 256 + 4 * lane;
@@ -111,6 +112,18 @@ __global__ void k_split_p(const float* __restrict__ P, int64_t ldp, int64_t m, i
   lo[idx] = to_bf16_bits(v - bf16_bits_to_f32(h));
 }
 
+template <bool TILED>
+void launch_pack(const float* X, int64_t ldx, int64_t N, int64_t k, uint8_t* codes, int64_t cstride,
+                 uint16_t* scales, int64_t sstride, int word_store, int64_t row0, int64_t steps_row,
+                 int64_t step0, hipStream_t s) {
+  auto* kfn = k <= 1024   ? k_sign_pack<TILED, 1>
+              : k <= 2048 ? k_sign_pack<TILED, 2>
+              : k <= 4096 ? k_sign_pack<TILED, 4>
+                          : k_sign_pack<TILED, 8>;
+  hipLaunchKernelGGL(kfn, dim3((unsigned)N), dim3(256), 0, s, X, ldx, N, k, codes, cstride, scales,
+                     sstride, word_store, row0, steps_row, step0);
+}
+
 }  // namespace
 
 eogp_status sign_pack(const float* X, int64_t ldx, int64_t N, int64_t k, uint8_t* codes,
@@ -118,9 +131,7 @@ eogp_status sign_pack(const float* X, int64_t ldx, int64_t N, int64_t k, uint8_t
   if (N == 0) return EOGP_OK;
   const int word_store = ((uintptr_t)codes % 4 == 0) && (cstride % 4 == 0);
   timing::Scope ts(EOGP_KT_SIGN_PACK, s);
-  hipLaunchKernelGGL(k_sign_pack<false>, dim3((unsigned)N), dim3(256), 0, s, X, ldx, N, k,
-                     codes, cstride, scales, sstride, word_store, (int64_t)0, (int64_t)0,
-                     (int64_t)0);
+  launch_pack<false>(X, ldx, N, k, codes, cstride, scales, sstride, word_store, 0, 0, 0, s);
   EOGP_LAUNCH_CHECK("sign_pack");
   return EOGP_OK;
 }
@@ -130,8 +141,7 @@ eogp_status sign_pack_tiled(const float* X, int64_t ldx, int64_t N, int64_t k, i
                             int64_t sstride, hipStream_t s) {
   if (N == 0) return EOGP_OK;
   timing::Scope ts(EOGP_KT_SIGN_PACK, s);
-  hipLaunchKernelGGL(k_sign_pack<true>, dim3((unsigned)N), dim3(256), 0, s, X, ldx, N, k, codes,
-                     (int64_t)0, scales, sstride, 0, row0, steps_row, step0);
+  launch_pack<true>(X, ldx, N, k, codes, 0, scales, sstride, 0, row0, steps_row, step0, s);
   EOGP_LAUNCH_CHECK("sign_pack (tiled)");
   return EOGP_OK;
 }

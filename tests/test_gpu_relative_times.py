@@ -149,3 +149,20 @@ def test_rows_a_power_of_two_apart_cost_little_more():
     even, odd = times(call(0), call(64))
     print(f"[times] 16 x 8,192 bits row-major: 16 KB apart {even:.1f} us, 64 bytes more {odd:.1f} us", flush=True)
     assert even <= 1.25 * odd
+
+
+def test_short_rows_pack_no_slower_than_their_bytes():
+    """Rows of 64 coordinates carry an eighth of the bytes of rows of 512: packing them
+    takes no longer."""
+    N = 100_000
+    X = torch.randn((N, 1024), device=DEV)
+    scales = torch.empty((N, 1), dtype=torch.int16, device=DEV)
+
+    def call(k):
+        x, codes = X[:, :k].contiguous(), torch.empty((N, k // 8), dtype=torch.uint8, device=DEV)
+        return lambda: E.eogp_sign_pack(x, codes, scales)
+
+    t64, t256, t1024 = times(call(64), call(256), call(1024))
+    print(f"[times] pack 100,000 rows: of 64 {t64:.1f} us, of 256 {t256:.1f} us, of 1,024 {t1024:.1f} us", flush=True)
+    # 410 MB are read for rows of 1,024: at 3 TB/s or better (2.2 when every row paid for eight chunks)
+    assert t1024 <= 137 and t64 <= 0.8 * t1024

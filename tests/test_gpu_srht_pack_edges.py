@@ -8,6 +8,7 @@ import torch
 from oracle import eogp_oracle as O
 from paper_2609_37842_amd import eogp as E
 from paper_2609_37842_amd import synth as S
+from tiled_helpers import tiled_from_rows
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -50,7 +51,7 @@ def test_srht_edges(m, k):
     assert err <= 1e-5                           # the largest of up to 2e5 entries, five times the rms bound
 
 
-@pytest.mark.parametrize("k", [1, 3, 7, 8, 9, 253, 256, 259, 1029, 8192, 8195, 16640])
+@pytest.mark.parametrize("k", [1, 3, 7, 8, 9, 253, 256, 259, 1023, 1024, 1029, 2047, 2049, 4096, 4099, 8192, 8195, 16640])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_sign_pack_edges(k, shift):
     """Codes are exact; a scale may differ by one fp16 step (2^-10) from the rounded fp64 mean."""
@@ -70,3 +71,19 @@ def test_sign_pack_edges(k, shift):
     assert np.all(got[:, :shift] == 0xA5) and np.all(got[:, shift + nb:] == 0xA5)
     ref = np.abs(x.astype(np.float64)).mean(1)
     assert np.all(np.abs(scales.cpu().numpy().view(np.float16)[:, 0] - ref) <= ref * 2.0 ** -10)
+
+
+@pytest.mark.parametrize("k", [512, 1024, 1536, 2048, 2560, 4096, 4608, 8704])
+def test_sign_pack_tiled_row_lengths(k):
+    """Every number of chunks that a wave requests at once: the tiled codes and scales are the
+    row-major ones, which test_sign_pack_edges checks."""
+    say(f"[sign_pack_tiled] k={k}")
+    N = 37
+    X = torch.from_numpy(np.random.default_rng(k).standard_normal((N, k)).astype(np.float32)).to(DEV)
+    rows, s0 = E.eogp_sign_pack(X)
+    tiles = torch.zeros(E.tiled_store_bytes(N, [k]), dtype=torch.uint8, device=DEV)
+    s1 = torch.empty((N, 1), dtype=torch.int16, device=DEV)
+    E.eogp_sign_pack_tiled(X, tiles, 0, k // 512, 0, s1)
+    torch.cuda.synchronize()
+    assert np.array_equal(tiles.cpu().numpy(), tiled_from_rows(rows.cpu().numpy()))
+    assert torch.equal(s0.view(torch.int16).view(-1), s1.view(-1))
