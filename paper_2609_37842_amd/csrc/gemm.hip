@@ -54,6 +54,7 @@
 #include <type_traits>
 
 #include "gemm.h"
+#include "gemm_plan.h"
 #include "timing.h"
 
 namespace eogp {
@@ -1194,23 +1195,19 @@ void pick(const KParams& kp, bool b16, unsigned grid, hipStream_t s) {
   else hipLaunchKernelGGL((k_gemm<AT, AP, BP, F16, BN, true>), dim3(grid), dim3(NTHR), 0, s, kp);
 }
 
-// k_gemm_skinny applies: at most 128 known rows, fp32 output in place, 16-bit
-// operand rows on 16-byte boundaries and K a multiple of 8. Above 128 rows the tiles of
+// k_gemm_skinny can run: known rows, fp32 output in place, 16-bit operand rows on
+// 16-byte boundaries and K a multiple of 8. Above 128 rows the tiles of
 // k_gemm_p are at least half full and the time is no longer B's stream alone.
-constexpr int64_t kSkinnyRows = 128;
 inline bool skinny(const GemmArgs& g, bool b16) {
   return b16 && g.M <= kSkinnyRows && !g.M_dev && !g.a_rows && !g.CT && g.a_scale == 1.f && g.K % 8 == 0;
 }
 template <int AT, int AP, int BP, bool F16>
-eogp_status launch_skinny(const GemmArgs& g, hipStream_t s) {
+eogp_status launch_skinny(const GemmArgs& g, const FewRowsPlan& plan, hipStream_t s) {
   SkinnyParams kp;
   kp.g = g;
-  kp.splits = 1;
-  const int64_t chunks = ceil_div(g.K, (int64_t)64), tiles = ceil_div(g.N, (int64_t)256);
-  if (g.partial)   // about two workgroups per CU, at least 8 chunks each
-    kp.splits = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)g.max_splits, ceil_div(2 * kCus, tiles), chunks / 8}));
-  kp.kc = ceil_div(chunks, (int64_t)kp.splits) * 64;
-  kp.splits = (int)ceil_div(g.K, kp.kc);
+  kp.splits = plan.splits;
+  kp.kc = plan.kc;
+  const int64_t tiles = ceil_div(g.N, (int64_t)256);
   timing::Scope ts(g.timing_class, s);
   const dim3 gd((unsigned)(tiles * kp.splits)), bd(512);
   if (g.M <= 32) hipLaunchKernelGGL((k_gemm_skinny<AT, AP, BP, F16, 1>), gd, bd, 0, s, kp);
@@ -1228,7 +1225,10 @@ template <int AT, int AP, int BP, bool F16>
 eogp_status launch(const GemmArgs& g, bool b16, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return EOGP_OK;
   if constexpr (AT != 2)
-    if (skinny(g, b16)) return launch_skinny<AT, AP, BP, F16>(g, s);
+    if (skinny(g, b16)) {
+      const FewRowsPlan plan = few_rows_plan(g.M, g.N, g.K, g.partial ? g.max_splits : 1, AP + BP - 1);
+      if (plan.use) return launch_skinny<AT, AP, BP, F16>(g, plan, s);
+    }
   const int64_t pad256 = ((g.N + 255) / 256) * 256, pad128 = ((g.N + 127) / 128) * 128;
   const bool wide = pad256 * 10 <= pad128 * 11;      // at most 10% more padding
   const int bn = wide ? 256 : 128;

@@ -166,3 +166,16 @@ def test_short_rows_pack_no_slower_than_their_bytes():
     print(f"[times] pack 100,000 rows: of 64 {t64:.1f} us, of 256 {t256:.1f} us, of 1,024 {t1024:.1f} us", flush=True)
     # 410 MB are read for rows of 1,024: at 3 TB/s or better (2.2 when every row paid for eight chunks)
     assert t1024 <= 137 and t64 <= 0.8 * t1024
+
+
+@pytest.mark.parametrize("m,k", [(32768, 1024), (16384, 4096)])
+def test_128_rows_cost_no_more_than_129(m, k):
+    """Up to 128 rows a kernel of their own may run; not where the one for more is faster."""
+    Z = torch.randn((129, m), device=DEV).half()
+    Pt = torch.randn((k, m), device=DEV).mul_(m ** -0.5).half()
+    ws = torch.empty(E.eogp_pca_project_workspace_size(129, m, k, E.F16, E.PREC_FAST), dtype=torch.uint8, device=DEV)
+    X = torch.empty((129, k), device=DEV)
+    few, more = times(lambda: E.eogp_pca_project(Z[:128], Pt, X=X[:128], ws=ws),
+                      lambda: E.eogp_pca_project(Z, Pt, X=X, ws=ws))
+    print(f"[times] {m} -> {k}: 128 rows {few:.1f} us, 129 rows {more:.1f} us", flush=True)
+    assert few <= 1.08 * more
