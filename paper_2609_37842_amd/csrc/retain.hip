@@ -25,6 +25,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "ekfac_plan.h"
 #include "gemm.h"
 #include "plan.h"
 #include "scan.h"
@@ -758,39 +759,6 @@ __global__ __launch_bounds__(256) void k_fill_zero(float* __restrict__ x, int64_
   if (e < n) x[e] = 0.f;
 }
 
-// Ranges of examples that a workspace always has room for.
-int sq16_min_splits(int64_t N, int64_t d_in, int64_t d_out) {
-  const int64_t groups = ceil_div(d_in, 128) * ceil_div(d_out, 128);
-  int64_t sp = ceil_div(2 * kCus, groups);
-  sp = std::min<int64_t>(sp, std::max<int64_t>(1, N / 4));
-  return (int)std::max<int64_t>(1, std::min<int64_t>(sp, 32));
-}
-
-// Example ranges of the fp16 squares when the scratch allows: eight (one XCD per
-// range), or for modules whose tiles are few the multiple of eight up to 32 that
-// fills the last round of two workgroups per CU best (the first at 90%), with at
-// least 4 examples per range.
-// More ranges where eight fill the chip cost more partial sums than the fuller round
-// gives: 128 examples of 3,073 x 768 took 1,401 us with 16 ranges, 1,345 at the start;
-// with eight 1,342 (1,400 at the start on that card).
-// Batches of fewer than 32 examples, and modules whose tiles alone fill the chip
-// (their partial sums would cost more than the shared L2 gives), take the fewest.
-int sq16_splits(int64_t N, int64_t d_in, int64_t d_out) {
-  const int64_t groups = ceil_div(d_in, 128) * ceil_div(d_out, 128);
-  if (N < 32 || groups >= 2 * kCus) return sq16_min_splits(N, d_in, d_out);
-  int best = 8;
-  double most = 0;
-  for (int sp = 8; sp <= 32 && sp * 4 <= N && groups * best < 2 * kCus; sp += 8) {
-    const double rounds = (double)(groups * sp) / (2 * kCus), full = rounds / std::ceil(rounds);
-    if (full > most) {
-      most = full;
-      best = sp;
-    }
-    if (full >= 0.9) break;
-  }
-  return best;
-}
-
 eogp_plan basis_plan(int64_t d_in, int64_t d_out) {
   eogp_plan q;
   q.d_out = d_out;
@@ -820,7 +788,7 @@ size_t ekfac_fixed_bytes(const eogp_plan& q, int64_t N, int64_t T) {
 size_t ekfac_ws(int64_t N, int64_t T, int64_t d_in, int64_t d_out) {
   const eogp_plan q = basis_plan(d_in, d_out);
   return ekfac_fixed_bytes(q, N, T) +
-         align256((size_t)std::max(sq16_splits(N, d_in, d_out), sq16_min_splits(N, d_in, d_out)) * d_out * d_in * 4);
+         align256((size_t)std::max(sq16_splits(N, T, d_in, d_out), sq16_min_splits(N, d_in, d_out)) * d_out * d_in * 4);
 }
 
 eogp_status ekfac_pass(const void* acts, int64_t ld_acts, const void* grads, int64_t ld_grads,
@@ -833,7 +801,7 @@ eogp_status ekfac_pass(const void* acts, int64_t ld_acts, const void* grads, int
   const size_t fixed = ekfac_fixed_bytes(q, N, T), sums = (size_t)d_out * d_in * 4;
   int splits = sq16_min_splits(N, d_in, d_out);
   if (ws_bytes < fixed + align256((size_t)splits * sums)) return fail(EOGP_ERR_WORKSPACE, "ekfac: workspace too small");
-  if (ws_bytes >= fixed + align256((size_t)sq16_splits(N, d_in, d_out) * sums)) splits = sq16_splits(N, d_in, d_out);
+  if (ws_bytes >= fixed + align256((size_t)sq16_splits(N, T, d_in, d_out) * sums)) splits = sq16_splits(N, T, d_in, d_out);
   if (N == 0) {                                  // an empty batch adds nothing
     if (!accumulate) {
       hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)ceil_div(d_out * d_in, 256)), dim3(256), 0, s,
