@@ -55,6 +55,14 @@ typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
 
 constexpr int kWave = 64;
 
+// Orders a wave's LDS accesses before it against those after it: what one lane wrote,
+// another lane of the wave may read, and what was read may be overwritten. (The LDS
+// serves a wave in order; this keeps the compiler from moving accesses across.)
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // fp64 -> fp16 bit pattern, round to nearest even, overflow -> inf (IEEE).
 __device__ __forceinline__ uint16_t f64_to_f16_rne(double x) {
   uint64_t u = __double_as_longlong(x);

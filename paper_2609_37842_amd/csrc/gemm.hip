@@ -1114,6 +1114,7 @@ __global__ __launch_bounds__(512) void k_gemm_skinny(SkinnyParams kp) {
     for (int p = 0; p < BP; ++p)
 #pragma unroll
       for (int i = 0; i < 4; ++i) *reinterpret_cast<v4u*>(&sB[wid][p][at(8 * i + b_r, b_c)]) = R.r[p][i];
+    wave_lds_order();                  // the wave's other lanes read them as fragments
     if (ch + PF < nc) load_b(ch + PF, R);
 #pragma unroll
     for (int j = 0; j < KC / 16; ++j) {
@@ -1137,7 +1138,7 @@ __global__ __launch_bounds__(512) void k_gemm_skinny(SkinnyParams kp) {
     }
     stage_a(st ^ 1, RA);               // chunk ch + 1 (past the end: a copy, unused)
     load_a(last(ch + 2), RA);
-    __syncthreads();
+    __syncthreads();                   // (also: the fragments are read before sB is written again)
   };
   for (int64_t ch = 0; ch < nc; ch += PF)
 #pragma unroll

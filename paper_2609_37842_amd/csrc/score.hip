@@ -334,6 +334,7 @@ __device__ __forceinline__ void prune_list(uint64_t* key, uint32_t* idx, int* cn
   uint64_t tk;
   uint32_t ti;
   wave_select<PER>(k, id, topk, tk, ti);
+  wave_lds_order();                          // every lane has read its entries
   wave_compact<PER>(k, id, tk, ti, key, idx);
   if (lane == 0) {
     *cnt = topk;
@@ -1047,7 +1048,9 @@ __device__ __forceinline__ int wave_topk(int total, int topk, uint64_t* key_o, u
     uint64_t tk = 0;
     uint32_t ti = 0xFFFFFFFEu;               // every entry that is not empty
     if (have > topk) wave_select<MRG_PER>(key, id, topk, tk, ti);
+    wave_lds_order();                        // every lane has read its slots
     wave_compact<MRG_PER>(key, id, tk, ti, key_o, idx_o);
+    wave_lds_order();                        // the next round reads other lanes' entries
     kept = have < topk ? have : topk;
     pos += kept - before_kept;               // the loop adds 512 less the new count
   }
