@@ -93,17 +93,6 @@ __device__ __forceinline__ uint32_t pack2(uint32_t lo, uint32_t hi) {
 }
 
 template <bool F16>
-__device__ __forceinline__ uint16_t cvt16(float v) {
-  if constexpr (F16) return to_f16_bits(v);
-  else return to_bf16_bits(v);
-}
-template <bool F16>
-__device__ __forceinline__ float back16(uint32_t b) {
-  if constexpr (F16) return f16_bits_to_f32((uint16_t)b);
-  else return bf16_bits_to_f32((uint16_t)b);
-}
-
-template <bool F16>
 __device__ __forceinline__ f32x16 mfma32(const v4u& a, const v4u& b, f32x16 c) {
   if constexpr (F16) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a),

@@ -48,7 +48,6 @@
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
-#include <utility>
 
 #include "common.h"
 #include "score_plan.h"
@@ -374,12 +373,6 @@ struct ScoreArgs {
   void* part;
   int64_t n_tiles;   // tiled store: 32-row tiles (ceil(N / 32))
 };
-
-// Calls f(integral_constant<I>) for I = 0 .. sizeof...(I) - 1 in order.
-template <typename F, int... I>
-__device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>, F&& f) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
 
 // NQT: groups of 16 queries per pass. RT: 32-row tiles per wave. NCLS:
 // accumulator classes of the bit expansion (1 or 2). MODE 0 / 3: one module (of
