@@ -1,14 +1,16 @@
 """Every variant of the scoring pass against the oracle, exactly: 16 and 32
-queries per pass, two and four row tiles per wave, one and several modules,
-dots of 32 and 64 bits, both store layouts, module ends inside a step, ties
-that fill the candidate lists, and a workspace that holds only the 16-query
-layout."""
+queries per pass, two and (tiled) four row tiles per wave, one and several
+modules, dots of 32 and 64 bits, both store layouts, rows requested by halves
+and whole steps, module ends inside a step, ties that fill the candidate lists,
+and a workspace that holds only the 16-query layout. Each case names the variant
+it is for and asserts that the plan takes it."""
 import numpy as np
 import pytest
 import torch
 
 import oracle as O
 from paper_2609_37842_amd import eogp as E
+from plan_helpers import score_plan
 from tiled_helpers import tiled_from_rows
 
 pytestmark = pytest.mark.gpu
@@ -44,21 +46,41 @@ def check(codes, scales, ks, Y, topk, tiled):
 
 
 @pytest.mark.parametrize("tiled", [True, False])
-@pytest.mark.parametrize("N,ks,Q,topk", [
-    (19, [1024], 5, 10),               # fewer rows than a tile
-    (5000, [2048], 16, 100),           # 16 queries, two tiles per wave
-    (5000, [2048], 40, 100),           # 32 queries, then a last pass of 16
-    (270_000, [512], 16, 200),         # 16 queries, four tiles per wave
-    (270_000, [512], 33, 128),         # 32 queries, four tiles per wave
-    (3000, [512, 1024], 16, 200),      # several modules
-    (3000, [512, 1024, 512], 20, 37),  # several modules, 32 queries
-    (30_000, [512] * 3, 16, 100),      # several modules, four tiles per wave
-    (30_000, [512] * 3, 33, 100),
-    (700, [66048], 20, 10),            # one module whose dots take 64 bits
-    (1100, [1 << 18, 512], 20, 10),    # 64-bit dots of several modules
+@pytest.mark.parametrize("N,ks,Q,topk,rt,nqt", [
+    (19, [1024], 5, 10, 2, 1),               # fewer rows than a tile
+    (5000, [2048], 16, 100, 2, 1),           # 16 queries, two tiles per wave
+    (5000, [2048], 40, 100, 2, 2),           # 32 queries, then a last pass of 16
+    (270_000, [512], 16, 200, 2, 1),         # three rounds of two-tile blocks
+    (270_000, [512], 33, 128, 2, 2),
+    (140_001, [512], 16, 200, 4, 1),         # four tiles per wave, an unfinished last block
+    (140_001, [512], 33, 100, 4, 2),
+    (140_001, [1024], 64, 128, 4, 2),
+    (500_001, [512], 16, 256, 4, 1),         # several blocks per workgroup: requests run on
+    (500_001, [512], 33, 100, 4, 2),
+    (3000, [512, 1024], 16, 200, 2, 1),      # several modules
+    (3000, [512, 1024, 512], 20, 37, 2, 2),  # several modules, 32 queries
+    (30_000, [512] * 3, 33, 100, 2, 2),
+    (70_001, [512] * 3, 16, 100, 4, 1),      # several modules, four tiles per wave
+    (70_001, [512] * 3, 33, 100, 4, 2),
+    (90_001, [512] * 20, 20, 10, 4, 2),      # several units per workgroup
+    (700, [66048], 20, 10, 2, 1),            # one module whose dots take 64 bits
+    (1100, [1 << 18, 512], 20, 10, 2, 1),    # 64-bit dots of several modules
 ])
-def test_score_pass_variants(N, ks, Q, topk, tiled):
-    check(*store(N, ks, Q, N + Q)[:2], ks, store(N, ks, Q, N + Q)[2], topk, tiled)
+def test_score_pass_variants(N, ks, Q, topk, rt, nqt, tiled):
+    plan = score_plan(N, Q, ks, topk, tiled)
+    assert (plan["rt"], plan["nqt"]) == (rt if tiled else 2, nqt)      # the kernel this case is for
+    if N in (500_001, 90_001) and tiled:
+        assert plan["n_blocks"] * plan["n_rng"] > plan["grid"]
+    codes, scales, Y = store(N, ks, Q, N + Q)
+    check(codes, scales, ks, Y, topk, tiled)
+
+
+@pytest.mark.parametrize("N,ks", [(140_001, [576]), (140_001, [64]), (30_001, [320, 64, 704])])
+@pytest.mark.parametrize("Q", [16, 33])
+def test_score_many_rows_end_inside_a_step(N, ks, Q):
+    """Row-major modules that end inside a half step, over more blocks than one round."""
+    codes, scales, Y = store(N, ks, Q, N + Q)
+    check(codes, scales, ks, Y, 20, False)
 
 
 @pytest.mark.parametrize("N,ks,Q", [
@@ -120,12 +142,11 @@ def test_score_workspace_of_the_16_query_layout(ks):
     L = E.load()
     karr = (E.c_i64 * len(ks))(*ks)
     full = E.eogp_score_topk_workspace_size(N, Q, ks, topk)
-    # lists of 16 queries (and dots of several modules) less than the 32-query layout's
-    lists = -(-N // 512) if len(ks) == 1 else -(-N // 64)
-    less = full - 16 * topk * 12 * lists - (16 * N * 4 * len(ks) if len(ks) > 1 else 0)
-    assert less < full
+    assert score_plan(N, Q, ks, topk, False) == dict(score_plan(N, Q, ks, topk, False, full), nqt=2, total=full)
+    less = score_plan(N, Q, ks, topk, False, 0)["total"]          # the 16-query layout
+    assert less < full and score_plan(N, Q, ks, topk, False, full - 1)["nqt"] == 1
     ws = torch.empty(full, dtype=torch.uint8, device=DEV)
-    for nbytes in (full, less):
+    for nbytes in (full, full - 1, less):
         i2, s2 = torch.full_like(idx, -7), torch.zeros_like(sc)
         st = L.eogp_score_topk(E._ptr(c), codes.shape[1], E._ptr(s), N, len(ks), karr, E._ptr(y), sum(ks), Q, topk,
                                E._ptr(i2), E._ptr(s2), None, E._ptr(ws), nbytes, E._stream())
@@ -133,4 +154,4 @@ def test_score_workspace_of_the_16_query_layout(ks):
         torch.cuda.synchronize()
         assert torch.equal(i2, idx) and torch.equal(s2, sc)
     assert L.eogp_score_topk(E._ptr(c), codes.shape[1], E._ptr(s), N, len(ks), karr, E._ptr(y), sum(ks), Q, topk,
-                             E._ptr(idx), E._ptr(sc), None, E._ptr(ws), less // 2, E._stream()) == -4
+                             E._ptr(idx), E._ptr(sc), None, E._ptr(ws), less - 1, E._stream()) == -4
