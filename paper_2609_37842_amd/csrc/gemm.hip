@@ -33,7 +33,7 @@
 // K-slice is processed first, by the only bounds-checked load. fp32 A rows may
 // start at any element: 16-byte loads need no more than element alignment (128
 // examples of an unpadded 769 -> 768 module in the accurate mode, whose A rows
-// were loaded element by element before: 423 -> 394 us).
+// were loaded element by element before: 402 -> 384 us).
 //
 // Precision. fp32 A is converted while it is staged: rounded to the MFMA type,
 // or split into high and low parts (accurate mode), whose cross terms
@@ -977,8 +977,8 @@ void k_gemm_p(KParams kp) {
 // ---- few rows: the second stage of a small batch ------------------------------
 // C[M, N] = A[M, K] B[N, K]^T for M <= 32 MT (MT = 1, 2, 4) and a B that is read
 // once: bound by B's stream from HBM. k_gemm_p works on 256-row tiles, so with
-// few rows it multiplies mostly padding (64 rows, 65,536 x 32,768 fp16 P: 1,140 us
-// for 4.3 GB; here 660 us, 6.5 TB/s).
+// few rows it multiplies mostly padding (64 rows, 65,536 x 32,768 fp16 P: 1,134 us
+// for 4.3 GB; here 652 us, 6.6 TB/s).
 //
 // A workgroup (8 waves) owns 256 columns and a K range, each wave 32 columns. A
 // wave streams its own B rows, 64 deep at a time (a whole 128-byte line of each

@@ -17,9 +17,10 @@
 // same lane). A 512-thread workgroup (8 waves, 2 per SIMD) owns 256 RT
 // consecutive rows at a time, each wave RT tiles of 32 rows. The modules are
 // walked in steps of 512 bits, each in two halves of 256: per half each lane
-// holds 16 bytes of each of its RT rows (requested two halves ahead), the
-// workgroup stages the half's plane fragments (8 KB per 16 queries) in LDS,
-// and every fragment read from LDS feeds RT MFMAs, every expanded code operand
+// holds 16 bytes of each of its RT rows (requested again as soon as they are used,
+// or, for row-major rows a multiple of 8 KB apart, both halves together a step
+// ahead), the workgroup stages the half's plane fragments (8 KB per 16 queries) in
+// LDS, and every fragment read from LDS feeds RT MFMAs, every expanded code operand
 // NQT of them. The requests run on into the next block of rows, so a block's
 // last halves and its candidate pass cover the next one's first loads.
 //

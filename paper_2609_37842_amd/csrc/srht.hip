@@ -10,7 +10,8 @@
 // 4 t + 4 NT j of the signed, zero-padded row (one load of z and one of the
 // signs per four elements) and transforms bits 0, 1 (inside a piece) and the
 // bits of j in registers; (b) the values go through LDS (written 16 bytes at a
-// time, read 64 consecutive words per wave: no bank conflicts, no padding) and
+// time; a wave reads 64 consecutive words at p = 2^10, 2^12 and 2^14, two runs of 32
+// at 2^11 and 2^13, and every other pair of words, half the banks, at 2^15) and
 // thread t takes the elements that differ in the next log2 E bits, which are
 // transformed in registers; the log2 NT - log2 E bits left are lane bits, their
 // butterflies read the other lane by DPP (or permlane16_swap), not through LDS;
