@@ -33,6 +33,18 @@ MEASURED = [
     (1, 800, 300, 3, True), (64, 4096, 256, 3, True), (128, 2048, 700, 3, True),
     (128, 16384, 1024, 3, True), (128, 32768, 16384, 3, True),
     (64, 800, 300, 3, False), (64, 800, 300, 2, True), (128, 16384, 300, 2, False), (128, 16384, 1024, 2, True),
+    # tiled units that leave a grid rounded down to the XCDs in a second round, and neighbours that don't
+    (87, 2680, 785, 1, True), (128, 2688, 1024, 1, True), (128, 3200, 700, 1, True), (128, 1472, 1300, 1, True),
+    (128, 3648, 2500, 1, True), (65, 2680, 300, 3, True), (128, 2688, 785, 2, True), (128, 1024, 785, 3, True),
+    (128, 800, 785, 2, False),
+    # more groups than CUs: rounds of either kernel
+    (1, 32768, 12000, 1, True), (16, 16392, 12000, 1, True), (32, 32768, 8400, 1, True),
+    (128, 20000, 10240, 1, False), (65, 32760, 20480, 1, False), (128, 32768, 10240, 1, False),
+    (128, 20000, 11264, 1, True), (128, 16384, 16384, 1, True), (16, 32760, 18432, 1, False),
+    (48, 20000, 14336, 1, True),
+    # 224 to 256 groups: rows of P a multiple of 8 KB apart, and others
+    (64, 16384, 8192, 1, True), (128, 8200, 8192, 1, False), (87, 16392, 8192, 1, False),
+    (64, 8200, 4096, 1, False), (16, 16392, 8192, 1, False),
 ]
 
 
