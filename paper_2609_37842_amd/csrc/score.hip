@@ -1000,7 +1000,7 @@ __global__ __launch_bounds__(FOLD_THR) void k_score_fold(FoldArgs a) {
 // 7.4). Only the final top-k is put in order. (Before, a
 // bitonic sort of up to 1,024 entries by the whole workgroup per 512 entries,
 // one barrier per exchange stage: 49 + 46 us for the two levels at 256 lists of
-// 100 for 16 queries, now 21 + 25 us for 32.)
+// 100 for 16 queries, now 15 + 17 us for 32.)
 constexpr int MRG_THR = 256, MRG_W = MRG_THR / 64, MRG_PER = 8;
 struct MergeList {
   uint64_t key[MRG_W][MAX_TOPK];
@@ -1129,8 +1129,8 @@ void launch_pass(int nqt, int rt, dim3 gd, const ScoreArgs& a, hipStream_t s) {
     }
     // Row-major rows a multiple of 8 KB apart: lines of a row fall into few sets of the
     // L2 and are gone before the step's second half asks again (48 modules of 8,192 bits,
-    // 20,000 codes: 1.40 GB fetched by halves, 0.87 at once), so whole steps are
-    // requested; other rows by halves, which keeps more of the wait covered.
+    // 20,000 codes: 1.6 times the fetches by halves), so whole steps are requested;
+    // other rows by halves, which keeps more of the wait covered.
     if constexpr (MODE == 1 && !TILED) {
       if (a.cstride % 8192 == 0) {
         if (nqt == 2) hipLaunchKernelGGL((k_score<2, 2, 1, MODE, 256, false, true>), gd, bd, 0, s, a);
